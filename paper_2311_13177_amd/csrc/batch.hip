@@ -33,7 +33,8 @@ void SliceGroup::drop_graph() {
 
 // One tile shape for a whole group (the kernels take it as template parameters): the
 // shape every session already uses if they agree, else the largest slice's shape when it
-// fits every slice, else that shape with two-row tiles, which always fits.
+// fits every slice, else that shape with two-row tiles, which always fits. Where that shape
+// is the plan's own choice, its projection rows follow the work of the whole group.
 static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
     const vp_session* big = sessions[0];
     bool same = true;
@@ -42,6 +43,13 @@ static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
         if (s->plan->voxels() > big->plan->voxels()) big = s;
     }
     Tiles t = big->layout->tiles;
+    if (t == big->plan->base_tiles && sessions.size() > 1) {
+        std::vector<const vp_plan*> plans;
+        for (const vp_session* s : sessions) plans.push_back(s->plan);
+        const int rows = proj_rows_for(plans);
+        same = same && rows == t.proj_rows;
+        t.proj_rows = rows;
+    }
     if (same) return t;
     for (const vp_session* s : sessions) {
         const Layout* L = nullptr;
@@ -68,6 +76,7 @@ vp_status group_build(SliceGroup* g, const std::vector<vp_session*>& sessions, c
     L.fft_n = ns ? sessions[0]->plan->n : 0;
     for (const vp_session* s : sessions)
         if (s->plan->n != L.fft_n) L.fft_n = 0;
+    for (const vp_session* s : sessions) L.odd = L.odd || (s->plan->n & 1);
     for (int i = 0; i < ns; ++i) {
         const vp_plan* p = sessions[i]->plan;
         const Layout* lay = nullptr;

@@ -1,5 +1,7 @@
 // Sheared spectral projection (Section 4.2 "Projection").
 
+#include <algorithm>
+
 #include "kcommon.h"
 
 namespace vp {
@@ -12,9 +14,19 @@ namespace vp {
 // e % NW, slot e / NW. Each lane owns one column and accumulates PPT rows for each of
 // its GW parts over the bins in ascending order.
 
-template <int GW, int PPT, int SE, int P, int NW>
-__global__ __launch_bounds__(64 * NW) void k_project(const KArgs a) {
+// The planes go from memory straight to LDS in a ring of D phases of P planes (pb bytes each),
+// D - 1 phases in flight, with one barrier per phase. LDS reads (9 cycles of a CU per row of a
+// part and bin) and the taps' arithmetic (8 cycles over its four SIMDs) bound it, then, where
+// the volume streams from HBM, its bytes. They overlap only between waves: staging without
+// registers leaves the kernel at 24 to 40 VGPRs and exact plane sizes fit three or more
+// eight-wave blocks on a CU. Measured (192^2 x 32 bins x 16 knots, 12 rows): 55 us with planes
+// staged through registers two phases deep, 43 us so; 256^2 x 32 bins, 12 parts: 34 and 20 us.
+// A software pipeline of the LDS reads (100 to 130 VGPRs, half the waves) was slower, as were
+// taps held in the lanes and reading the planes through the vector cache without LDS.
+template <int GW, int PPT, int SE, int P, int D, int UB, int NW>
+__global__ __launch_bounds__(64 * NW) void k_project(const KArgs a, int pb) {
     extern __shared__ float2 sm[];
+    using Sg = DmaStager<SE, UB, 64 * NW>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (a.snap) step_snapshot(a);
@@ -29,9 +41,10 @@ __global__ __launch_bounds__(64 * NW) void k_project(const KArgs a) {
         const size_t nn = (size_t)n * n;
         const AS4 ProjGroup* gr = cst(DF(groups)) + tk->a;
         const int knot = gr->knot, ge0 = gr->e0, gne = gr->ne;
-        const int oxmin = gr->ox_min, oymin = gr->oy_min;
-        const int RH = PPT + gr->oy_max - oymin + 1, RW = kTileW + gr->ox_max - oxmin + 1;
-        const int RE = RH * RW;
+        // (16-byte units: from an even column, an even number of columns)
+        const int oxmin = UB == 16 ? gr->ox_min & ~1 : gr->ox_min, oymin = gr->oy_min;
+        const int RH = PPT + gr->oy_max - oymin + 1;
+        const int RW = UB == 16 ? (kTileW + gr->ox_max - oxmin + 2) & ~1 : kTileW + gr->ox_max - oxmin + 1;
         const int y0 = tk->b * PPT, x0 = tk->c * kTileW;
         const AS4 KnotEntry* ent = cst(DF(knot_ent));
         const AS4 ShearEntry* shear = cst(DF(shear));
@@ -56,48 +69,34 @@ __global__ __launch_bounds__(64 * NW) void k_project(const KArgs a) {
         for (int j = 0; j < GW; ++j)
 #pragma unroll
             for (int i = 0; i < PPT; ++i) acc[j][i] = make_float2(0.f, 0.f);
-        Stager<SE, P, 64 * NW> sg;
-        sg.init(RH, RW, y0 + oymin, x0 + oxmin, n);
-        float2 pre[P][SE];
-        {
-            const float2* planes[P];
+        Sg sg;
+        sg.init(RH, RW, y0 + oymin, x0 + oxmin, n, pb);
+        const int phase = P * pb;
+        auto issue = [&](int s0, int slot) {
 #pragma unroll
-            for (int p = 0; p < P; ++p) planes[p] = p < S ? V + (size_t)p * nn : nullptr;
-            sg.fetch(planes, (int)nn, pre);
-        }
-        for (int s0 = 0, it = 0; s0 < S; s0 += P, ++it) {
-            float2* buf = sm + (it & 1) * P * RE;
-            sg.store(buf, pre);
-            __syncthreads();
-            if (s0 + P < S) {
-                const float2* planes[P];
+            for (int p = 0; p < P; ++p)
+                sg.issue(s0 + p < S ? V + (size_t)(s0 + p) * nn : nullptr, (int)nn, slot * phase + p * pb);
+        };
 #pragma unroll
-                for (int p = 0; p < P; ++p) planes[p] = s0 + P + p < S ? V + (size_t)(s0 + P + p) * nn : nullptr;
-                sg.fetch(planes, (int)nn, pre);
-            }
+        for (int d = 0; d < D - 1; ++d) issue(d * P, d);
+        int slot = 0;
+        for (int s0 = 0; s0 < S; s0 += P) {
+            // this phase has landed for every wave, and every wave is done with the one before,
+            // whose slot takes the phase D - 1 ahead
+            sg.template wait<(D - 2) * P>();
+            issue(s0 + (D - 1) * P, slot == 0 ? D - 1 : slot - 1);
+            const float2* buf = sm + slot * (phase / 8);
+            slot = slot + 1 == D ? 0 : slot + 1;
 #pragma unroll
             for (int p = 0; p < P; ++p) {
                 const int s = s0 + p;
                 if (s < S) {
-                    // the bin's taps for every part of the wave, loaded before any is used
-                    // (a part slot without a part reads blade 0's entry and is skipped)
-                    int tox[GW], toy[GW];
-                    float tw[GW][4];
-#pragma unroll
-                    for (int j = 0; j < GW; ++j) {
-                        const AS4 ShearEntry* sh = shear + eb[j] * S + s;
-                        tox[j] = sh->ox;
-                        toy[j] = sh->oy;
-                        tw[j][0] = sh->w00;
-                        tw[j][1] = sh->w01;
-                        tw[j][2] = sh->w10;
-                        tw[j][3] = sh->w11;
-                    }
 #pragma unroll
                     for (int j = 0; j < GW; ++j) {
                         if (act[j]) {
-                            const float w00 = tw[j][0], w01 = tw[j][1], w10 = tw[j][2], w11 = tw[j][3];
-                            const float2* L = buf + p * RE + (toy[j] - oymin) * RW + (tox[j] - oxmin) + lane;
+                            const AS4 ShearEntry* sh = shear + eb[j] * S + s;
+                            const float w00 = sh->w00, w01 = sh->w01, w10 = sh->w10, w11 = sh->w11;
+                            const float2* L = buf + p * (pb / 8) + (sh->oy - oymin) * RW + (sh->ox - oxmin) + lane;
                             float2 a0 = L[0], a1 = L[1];
 #pragma unroll
                             for (int i = 0; i < PPT; ++i) {
@@ -116,7 +115,7 @@ __global__ __launch_bounds__(64 * NW) void k_project(const KArgs a) {
                 }
             }
         }
-        __syncthreads();
+        sg.template wait<0>();  // nothing of this item lands in the LDS of the next
         const int x = x0 + lane;
 #pragma unroll
         for (int j = 0; j < GW; ++j) {
@@ -136,31 +135,38 @@ __global__ __launch_bounds__(64 * NW) void k_project(const KArgs a) {
 
 static inline int grid_for(int ntasks) { return ntasks < 1 ? 1 : (ntasks > (1 << 20) ? (1 << 20) : ntasks); }
 
-// The staging depth (planes per phase, elements per thread) follows the region size as
-// for 256 threads; 512 threads need half the elements each (rounded up).
-template <int GW, int PPT>
-static void project_variant(const KArgs& a, int waves, int re, hipStream_t s) {
-    const dim3 g(grid_for(a.ntasks)), b(64 * waves);
-    const int depth = stage_depth(re);
-    const size_t lds = stage_lds_bytes(re);
-    if (waves == 8) {
-        if (depth == 5) hipLaunchKernelGGL((k_project<GW, PPT, 3, 3, 8>), g, b, lds, s, a);
-        else if (depth == 8) hipLaunchKernelGGL((k_project<GW, PPT, 4, 2, 8>), g, b, lds, s, a);
-        else hipLaunchKernelGGL((k_project<GW, PPT, 8, 1, 8>), g, b, lds, s, a);
-    } else {
-        if (depth == 5) hipLaunchKernelGGL((k_project<GW, PPT, 5, 3, 4>), g, b, lds, s, a);
-        else if (depth == 8) hipLaunchKernelGGL((k_project<GW, PPT, 8, 2, 4>), g, b, lds, s, a);
-        else hipLaunchKernelGGL((k_project<GW, PPT, 16, 1, 4>), g, b, lds, s, a);
-    }
+// Units per thread, planes per phase and phases of the ring (at most 64 KiB) follow the largest
+// region of the launch.
+template <int GW, int PPT, int NW>
+static void project_variant(const KArgs& a, int re, bool odd, hipStream_t s) {
+    const dim3 g(grid_for(a.ntasks)), b(64 * NW);
+    constexpr int W = 8 / NW;
+    // a plane's LDS bytes: whole chunks of a wave's units, at least as many as SE asks for
+    auto plane = [&](int se, int ub) { return std::max((re * 8 + 64 * ub - 1) / (64 * ub), (se - 1) * NW + 1) * 64 * ub; };
+#define PL(SE, P, D, UB)                                                                           \
+    do {                                                                                           \
+        const int pb = plane(SE, UB);                                                              \
+        hipLaunchKernelGGL((k_project<GW, PPT, SE, P, D, UB, NW>), g, b, (D) * (P) * pb, s, a, pb); \
+    } while (0)
+    if (re > 2048) PL(16 * W, 1, 2, 4);
+    else if (odd && re > 1024) PL(8 * W, 1, 3, 4);
+    else if (odd) PL(4 * W, 1, 4, 4);
+    else if (re > 1024) PL(2 * W, 1, 3, 16);
+    else if (NW == 4 && re <= 512) PL(1, 2, 2, 16);
+    else PL(W, 2, 2, 16);
+#undef PL
 }
 
-hipError_t launch_project(const KArgs& a, int rows, int gw, int waves, int re, hipStream_t s) {
+hipError_t launch_project(const KArgs& a, int rows, int gw, int waves, int re, bool odd, hipStream_t s) {
     if (a.ntasks <= 0) return hipSuccess;
     if (!proj_tiles_ok(rows, gw) || !item_waves_ok(waves) || re < 1 || re > kStageMax * kThreads)
         return hipErrorInvalidValue;
-#define PV(R, G)                                          \
-    case R * 16 + G:                                      \
-        if constexpr (proj_tiles_ok(R, G)) project_variant<G, R>(a, waves, re, s); \
+#define PV(R, G)                                                            \
+    case R * 16 + G:                                                        \
+        if constexpr (proj_tiles_ok(R, G)) {                                \
+            if (waves == 8) project_variant<G, R, 8>(a, re, odd, s);        \
+            else project_variant<G, R, 4>(a, re, odd, s);                   \
+        }                                                                   \
         break
     switch (rows * 16 + gw) {
         PV(1, 1); PV(1, 2); PV(1, 4); PV(1, 8);

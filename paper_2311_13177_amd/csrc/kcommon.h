@@ -24,6 +24,15 @@ __device__ __forceinline__ const AS4 T* cst(const T* p) {
     return (const AS4 T*)(const void*)p;
 }
 
+// Device memory as such: a pointer that the compiler cannot trace to a kernel argument is
+// otherwise accessed through flat instructions, which share the LDS counter and make every
+// later wait of the kernel a wait for all loads in flight.
+#define AS1 __attribute__((address_space(1)))
+template <class T>
+__device__ __forceinline__ AS1 T* glb(T* p) {
+    return (AS1 T*)p;
+}
+
 // Field of the work item's slice descriptor (descriptor array or the inline copy).
 #define DF(field) (a.descs ? cst(a.descs + slice)->field : a.one.field)
 
@@ -75,7 +84,7 @@ __device__ __forceinline__ int read_step_at(const int* stepp, int snap) {
 __device__ __forceinline__ void step_snapshot(const KArgs& a) {
     if (blockIdx.x != 0) return;
     for (int slice = threadIdx.x; slice < a.nslices; slice += blockDim.x) {
-        int* const stepp = a.descs ? a.descs[slice].step : a.one.step;
+        AS1 int* const stepp = glb(a.descs ? a.descs[slice].step : a.one.step);
         if (stepp) stepp[kSnapWord] = *stepp;
     }
 }
@@ -85,7 +94,7 @@ __device__ __forceinline__ void step_snapshot(const KArgs& a) {
 __device__ __forceinline__ void step_advance(const KArgs& a) {
     if (blockIdx.x != 0) return;
     for (int slice = threadIdx.x; slice < a.nslices; slice += blockDim.x) {
-        int* const stepp = a.descs ? a.descs[slice].step : a.one.step;
+        AS1 int* const stepp = glb(a.descs ? a.descs[slice].step : a.one.step);
         const int limit = a.descs ? a.descs[slice].step_limit : a.one.step_limit;
         if (stepp) {
             const int st = stepp[kSnapWord];
@@ -128,6 +137,20 @@ __device__ __forceinline__ float2 buffer_c64(__amdgpu_buffer_rsrc_t r, int idx) 
     return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, byte, 0, 0));
 }
 
+// Raw buffer load and store of one complex value at byte offsets voff (per lane) and
+// soff (uniform); loads beyond the buffer read zero, stores there are dropped.
+// CP is the cache-policy operand (epi_cache): 0, or non-temporal for streamed data.
+template <int CP = 0>
+__device__ __forceinline__ float2 buf_ld(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, CP));
+}
+template <int CP = 0>
+__device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, float2 v, int voff, int soff) {
+    using v2 = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2, v), r, voff, soff, CP);
+}
+
+using f32x4 = float __attribute__((ext_vector_type(4)));
 // ------------------------------------------------------------------ LDS staging
 //
 // A rectangular region (rows x cols) of an n x n image, origin (gy0, gx0), is staged
@@ -153,6 +176,54 @@ __device__ __forceinline__ float2 lane_f2(float2 v, int l) {
                        __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v.y), l)));
 }
 
+// A region staged straight from memory into LDS (buffer loads with an LDS destination: no
+// registers hold the data, so several planes can be in flight behind the barriers). The
+// region is linear in LDS; thread t moves units t, t + NT, ... of it, a unit being UB = 16
+// bytes (two complex values: regions of an even number of columns from an even origin, where
+// n is even) or 4 bytes (any region). Units outside the image are out of the buffer's range
+// and write zeros. A plane takes pb bytes of LDS, SE NT UB >= pb > (SE - 1) NT UB, a multiple
+// of a wave's 64 units; a wave issues SE loads per plane, or SE - 1 where its last chunk lies
+// past pb, whatever the item's own region, so it can wait for a plane by count.
+template <int SE, int UB, int NT>
+struct DmaStager {
+    int off[SE];
+    bool full;  // whether this wave issues SE loads per plane
+    __device__ void init(int rows, int cols, int gy0, int gx0, int n, int pb) {
+        const int w = cols * 8 / UB;  // units per region row
+        full = __builtin_amdgcn_readfirstlane(((threadIdx.x & ~63) + (SE - 1) * NT) * UB) < pb;
+#pragma unroll
+        for (int k = 0; k < SE; ++k) {
+            const int i = threadIdx.x + k * NT;
+            const int r = i / w, u = i - r * w;
+            const int gy = gy0 + r, gx = gx0 + u * UB / 8;
+            const bool in = r < rows && gy >= 0 && gy < n && gx >= 0 && gx < n;
+            off[k] = in ? (gy * n + gx0) * 8 + u * UB : kBufferOut;
+        }
+    }
+    // Issues the loads of a plane (a null plane: zeros) into LDS at byte offset `lds`.
+    __device__ void issue(const float2* plane, int nn, unsigned lds) const {
+        const __amdgpu_buffer_rsrc_t r = plane_rsrc(plane, plane ? nn : 0);
+        const unsigned base = __builtin_amdgcn_readfirstlane(lds + (threadIdx.x & ~63) * UB);
+#pragma unroll
+        for (int k = 0; k < SE; ++k) {
+            if (k == SE - 1 && !full) continue;
+            // M0 holds the wave's LDS base (one wait state before its use); lane l writes the
+            // l-th unit from there
+            if constexpr (UB == 16)
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(base + k * NT * UB), "v"(off[k]), "s"(r) : "memory", "m0");
+            else
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(base + k * NT * UB), "v"(off[k]), "s"(r) : "memory", "m0");
+        }
+    }
+    // Waits until at most `planes` planes of this wave's loads are outstanding and its LDS reads
+    // have returned, then for the block's other waves: LDS that every wave has staged and
+    // waited for is then readable, and LDS that every wave has read may be staged again.
+    template <int PLANES>
+    __device__ void wait() const {
+        if (full) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PLANES * SE) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PLANES * (SE - 1)) : "memory");
+    }
+};
 template <int SE, int P, int NT = kThreads>
 struct Stager {
     int off[SE];

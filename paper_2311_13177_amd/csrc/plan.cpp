@@ -128,14 +128,18 @@ static vp_status build_layout(const vp_plan* p, const Tiles& t, Layout* L) {
         }
     }
     L->re_proj = 1;
-    for (const ProjGroup& gr : L->groups)
+    int re_even = 1;  // the same regions from even columns, even columns wide
+    for (const ProjGroup& gr : L->groups) {
         L->re_proj = std::max(L->re_proj, region(t.proj_rows, gr.ox_min, gr.ox_max, gr.oy_min, gr.oy_max));
+        re_even = std::max(re_even, region(t.proj_rows, gr.ox_min & ~1, gr.ox_max | 1, gr.oy_min, gr.oy_max));
+    }
     L->re_gath = 1;
     for (const KnotInfo& ki : p->knots)
         L->re_gath = std::max(L->re_gath, region(t.gath_rows, ki.ox_min, ki.ox_max, ki.oy_min, ki.oy_max));
     if (L->re_proj > kStageMax * kThreads || L->re_gath > kStageMax * kThreads)
         return fail(VP_ERR_UNSUPPORTED, "tile shape (%d, %d, %d, %d): staged region exceeds the LDS staging",
                     t.proj_rows, t.proj_gw, t.gath_rows, t.gath_sc);
+    L->re_proj = std::max(L->re_proj, re_even);
     L->lds_res = 0;
     if (t.gath_res) {
         // every part of a knot resident at once: part j of knot kt at [j * region, (j + 1) * region)
@@ -194,16 +198,32 @@ static int pow2_ceil(int v) {
     return r;
 }
 
+// The tallest projection tile that still makes twelve waves with a part per CU over the plans
+// of one launch: a taller tile stages less halo per row (192^2 x 16 knots: 8 rows 48 us, 4 rows
+// 57; the tuner also tries 12 rows, 43 us), fewer waves leave CUs idle (256^2, one knot of 12
+// parts: 4 rows 20 us, 8 rows 23).
+int proj_rows_for(const std::vector<const vp_plan*>& plans) {
+    for (int rows : {8, 4, 2}) {
+        uint64_t waves = 0;
+        for (const vp_plan* p : plans)
+            waves += (uint64_t)p->knot_ent.size() * ceil_div(p->n, rows) * ceil_div(p->n, kTileW);
+        if (waves >= 12 * 256) return rows;
+    }
+    return 1;
+}
+
 Tiles heuristic_tiles(const vp_plan* p) {
-    // Eight-wave items over tall tiles, the shapes the tuner mostly picks on this device:
-    // a projection item projects 8 * proj_gw parts of one knot over 8 rows (4 below n =
-    // 192); a gather item covers 8 * gath_sc bins (all of S up to 64) over 4 rows, with
-    // every part of its knot resident in LDS (the plan falls back to parts staged a few at
-    // a time where they do not fit).
+    // Projection items: eight waves (a part of the knot each), or four where that leaves fewer
+    // waves of a knot's last group without a part (12 parts of 256^2 x 32 bins: 20 us in three
+    // groups of four, 21 us in eight and four; 34 us with two parts per wave in one group).
+    // Gather items cover 8 * gath_sc bins (all of S up to 64) over 4 rows, with every part of
+    // the knot resident in LDS (the plan falls back to parts staged a few at a time where they
+    // do not fit).
     Tiles t;
-    t.proj_w = 8;
-    t.proj_rows = p->n >= 192 ? 8 : 4;
-    t.proj_gw = p->max_knot_parts > 8 ? 2 : 1;
+    const int np = std::max(1, p->max_knot_parts);
+    t.proj_w = np <= 4 || (np > 8 && ceil_div(np, 4) * 4 < ceil_div(np, 8) * 8) ? 4 : 8;
+    t.proj_gw = 1;
+    t.proj_rows = proj_rows_for({p});
     t.gath_w = 8;
     t.gath_rows = 4;
     t.gath_sc = std::min(8, pow2_ceil(ceil_div(p->S, 8)));

@@ -148,6 +148,8 @@ vp_status plan_tables(const vp_plan* plan, DeviceTables** out);
 vp_status plan_layout(const vp_plan* plan, const Tiles& t, const Layout** out);
 // A layout's tables on the device of `tabs`, uploaded on first use.
 vp_status device_layout(const vp_plan* plan, DeviceTables* tabs, const Layout* L, const DeviceLayout** out);
+// Rows of the projection tiles for one launch over these plans.
+int proj_rows_for(const std::vector<const vp_plan*>& plans);
 // Tile shape chosen without measuring, from the plan's sizes.
 Tiles heuristic_tiles(const vp_plan* plan);
 

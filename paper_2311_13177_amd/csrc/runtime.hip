@@ -208,7 +208,7 @@ void launch_step(const KArgs& base, const StageLists& L, hipStream_t s, hipError
     a.nslices = L.n_slices;
     a.snap = 1;
     a.tasks = L.proj; a.ntasks = L.n_proj;
-    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, s)) != hipSuccess) { *err = e; return; }
+    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, s)) != hipSuccess) { *err = e; return; }
     a.snap = 0;
     MARK(1);
     a.tasks = L.rows; a.ntasks = L.n_rows;
@@ -251,6 +251,7 @@ StageLists plan_lists(const vp_plan* p, const DeviceTables* t, const Layout* lay
     L.render = t->t_render; L.n_render = (int)p->t_render.size();
     L.tiles = lay->tiles;
     L.fft_n = p->n;
+    L.odd = p->n & 1;
     L.re_proj = lay->re_proj; L.lds_rows = p->lds_rows; L.lds_cols = p->lds_cols; L.re_gath = lay->re_gath;
     L.lds_res = lay->lds_res;
     return L;
@@ -319,7 +320,7 @@ extern "C" vp_status vp_forward(const vp_plan* p, const vp_c64* d_vol, const vp_
     const StageLists L = plan_lists(p, sc.t, sc.lay, sc.dl);
     hipError_t e;
     a.tasks = L.proj; a.ntasks = L.n_proj;
-    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, sc.s)) != hipSuccess)
+    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, sc.s)) != hipSuccess)
         return hip_status(e, "vp_forward project");
     a.tasks = L.rows; a.ntasks = L.n_rows;
     if ((e = launch_rows(a, -1, L.fft_n, L.lds_rows, sc.s)) != hipSuccess) return hip_status(e, "vp_forward rows");
@@ -435,7 +436,7 @@ extern "C" vp_status vp_forward_noalloc(const vp_plan* p, const vp_c64* d_vol, c
     a.one.work = work;
     const StageLists L = plan_lists(p, t, lay, dl);
     a.tasks = L.proj; a.ntasks = L.n_proj;
-    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, s)) != hipSuccess)
+    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, s)) != hipSuccess)
         return hip_status(e, "vp_forward_noalloc project");
     a.tasks = L.rows; a.ntasks = L.n_rows;
     if ((e = launch_rows(a, -1, L.fft_n, L.lds_rows, s)) != hipSuccess) return hip_status(e, "vp_forward_noalloc rows");
@@ -605,7 +606,7 @@ extern "C" vp_status vp_nu_forward(const vp_plan* p, const vp_c64* d_vol, const 
     const StageLists L = plan_lists(p, sc.t, sc.lay, sc.dl);
     hipError_t e;
     a.tasks = L.proj; a.ntasks = L.n_proj;
-    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, sc.s)) != hipSuccess)
+    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, sc.s)) != hipSuccess)
         return hip_status(e, "vp_nu_forward project");
     nu.d.work = sc.work;
     nu.d.y = (const float2*)d_y;
@@ -706,7 +707,7 @@ struct vp_nu_session {
         a.snap = 1;  // snapshot of the step counter for the step's last kernel
         a.nslices = 1;
         hipError_t r = ev ? hipEventRecord(ev[0], str) : hipSuccess;
-        if (r == hipSuccess) r = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, str);
+        if (r == hipSuccess) r = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, str);
         if (r == hipSuccess && ev) r = hipEventRecord(ev[1], str);
         if (r == hipSuccess) r = nu.pass(NuScope::ROWS_FWD);
         if (r == hipSuccess && ev) r = hipEventRecord(ev[2], str);
@@ -1190,7 +1191,7 @@ vp_status session_objective_enqueue(vp_session* s, hipStream_t stream) {
     a.one.step_limit = 0x7fffffff;
     const StageLists& L = s->lists;
     a.tasks = L.proj; a.ntasks = L.n_proj;
-    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, stream)) != hipSuccess)
+    if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, stream)) != hipSuccess)
         return hip_status(e, "objective");
     a.tasks = L.rows; a.ntasks = L.n_rows;
     if ((e = launch_rows(a, -1, L.fft_n, L.lds_rows, stream)) != hipSuccess) return hip_status(e, "objective");

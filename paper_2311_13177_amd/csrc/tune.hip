@@ -144,7 +144,7 @@ vp_status tune_plan(const vp_plan* p, const vp_options* o, Tiles* out) {
                 float ms = 0.f;
                 st = time_launches(
                     s->stream, kReps,
-                    [&] { return launch_project(a, rows, gw, waves, L->re_proj, s->stream); }, &ms);
+                    [&] { return launch_project(a, rows, gw, waves, L->re_proj, p->n & 1, s->stream); }, &ms);
                 if (st != VP_OK) return st;
                 if (ms < best_ms) {
                     best_ms = ms;

@@ -17,19 +17,6 @@ struct UpdateArgs {
 };
 
 
-// Raw buffer load and store of one complex value at byte offsets voff (per lane) and
-// soff (uniform); loads beyond the buffer read zero, stores there are dropped.
-// CP is the cache-policy operand (epi_cache): 0, or non-temporal for streamed data.
-template <int CP = 0>
-__device__ __forceinline__ float2 buf_ld(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, CP));
-}
-template <int CP = 0>
-__device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, float2 v, int voff, int soff) {
-    using v2 = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2, v), r, voff, soff, CP);
-}
-
 // One voxel's regulariser gradient plus its data gradient `acc`, then the optimiser
 // update (Section 4.3): v0 the voxel at column x, row y, with x neighbours left/right,
 // time neighbours tp/tn, the Charbonnier weights of its differences with the previous
