@@ -34,7 +34,7 @@ void SliceGroup::drop_graph() {
 // One tile shape for a whole group (the kernels take it as template parameters): the
 // shape every session already uses if they agree, else the largest slice's shape when it
 // fits every slice, else that shape with two-row tiles, which always fits. Where that shape
-// is the plan's own choice, its projection rows follow the work of the whole group.
+// is the plan's own choice, its rows and bins per wave follow the work of the whole group.
 static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
     const vp_session* big = sessions[0];
     bool same = true;
@@ -45,10 +45,15 @@ static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
     Tiles t = big->layout->tiles;
     if (t == big->plan->base_tiles && sessions.size() > 1) {
         std::vector<const vp_plan*> plans;
-        for (const vp_session* s : sessions) plans.push_back(s->plan);
-        const int rows = proj_rows_for(plans);
-        same = same && rows == t.proj_rows;
-        t.proj_rows = rows;
+        uint64_t voxels = 0;
+        for (const vp_session* s : sessions) {
+            plans.push_back(s->plan);
+            voxels += s->plan->voxels();
+        }
+        t.proj_rows = proj_rows_for(plans);
+        gather_shape_for(voxels, big->plan->S, &t.gath_rows, &t.gath_sc);
+        if (!t.gath_res) t.gath_sc = std::min(t.gath_sc, 16 / t.gath_rows);
+        same = same && t == big->layout->tiles;
     }
     if (same) return t;
     for (const vp_session* s : sessions) {

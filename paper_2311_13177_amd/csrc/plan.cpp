@@ -212,21 +212,30 @@ int proj_rows_for(const std::vector<const vp_plan*>& plans) {
     return 1;
 }
 
+// Rows and bins per wave of the gather for one launch over this many voxels: up to 4 rows by
+// the bins that cover S with eight waves, less where that leaves fewer than sixteen waves per
+// CU (256^2 x 32 bins: 4 x 4 50 us, 4 x 2 37 us, 4 x 1 44 us; 64^2 x 16: 4 x 2 19 us, 4 x 1 15 us,
+// 2 x 1 13 us).
+void gather_shape_for(uint64_t voxels, int S, int* rows, int* sc) {
+    const uint64_t per_lane = voxels / (64 * 16 * 256);  // voxels a lane may take
+    *rows = per_lane >= 4 ? 4 : 2;
+    *sc = std::min(8, pow2_ceil(ceil_div(S, 8)));
+    while (*sc > 1 && (uint64_t)(*rows * *sc) > per_lane) *sc /= 2;
+}
+
 Tiles heuristic_tiles(const vp_plan* p) {
     // Projection items: eight waves (a part of the knot each), or four where that leaves fewer
     // waves of a knot's last group without a part (12 parts of 256^2 x 32 bins: 20 us in three
     // groups of four, 21 us in eight and four; 34 us with two parts per wave in one group).
-    // Gather items cover 8 * gath_sc bins (all of S up to 64) over 4 rows, with every part of
-    // the knot resident in LDS (the plan falls back to parts staged a few at a time where they
-    // do not fit).
+    // Gather items have every part of the knot resident in LDS (the plan falls back to parts
+    // staged a few at a time where they do not fit).
     Tiles t;
     const int np = std::max(1, p->max_knot_parts);
     t.proj_w = np <= 4 || (np > 8 && ceil_div(np, 4) * 4 < ceil_div(np, 8) * 8) ? 4 : 8;
     t.proj_gw = 1;
     t.proj_rows = proj_rows_for({p});
     t.gath_w = 8;
-    t.gath_rows = 4;
-    t.gath_sc = std::min(8, pow2_ceil(ceil_div(p->S, 8)));
+    gather_shape_for(p->voxels(), p->S, &t.gath_rows, &t.gath_sc);
     t.gath_res = 1;
     return t;
 }

@@ -150,6 +150,8 @@ vp_status plan_layout(const vp_plan* plan, const Tiles& t, const Layout** out);
 vp_status device_layout(const vp_plan* plan, DeviceTables* tabs, const Layout* L, const DeviceLayout** out);
 // Rows of the projection tiles for one launch over these plans.
 int proj_rows_for(const std::vector<const vp_plan*>& plans);
+// Rows and bins per wave of the gather items for one launch over `voxels` voxels.
+void gather_shape_for(uint64_t voxels, int S, int* rows, int* sc);
 // Tile shape chosen without measuring, from the plan's sizes.
 Tiles heuristic_tiles(const vp_plan* plan);
 
