@@ -79,8 +79,29 @@ vp_status group_build(SliceGroup* g, const std::vector<vp_session*>& sessions, c
     StageLists L;
     if (ns) L.tiles = group_tiles(sessions);
     L.fft_n = ns ? sessions[0]->plan->n : 0;
-    for (const vp_session* s : sessions)
-        if (s->plan->n != L.fft_n) L.fft_n = 0;
+    // the row and column items by kind of length: compile-time plans up to 384, 512, any other
+    auto kind = [&](int i) {
+        const int n = sessions[i]->plan->n;
+        return !fft_compiled(n) ? 2 : (n > 384 ? 1 : 0);
+    };
+    for (int k = 0; k < 3; ++k) {
+        FftSegment seg;
+        seg.rows0 = (int)rows.size();
+        seg.cols0 = (int)cols.size();
+        seg.n = kMaxN + 1;  // none yet
+        for (int i = 0; i < ns; ++i) {
+            if (kind(i) != k) continue;
+            const vp_plan* p = sessions[i]->plan;
+            for (Task t : p->t_rows) { t.slice = i; rows.push_back(t); }
+            for (Task t : p->t_cols) { t.slice = i; cols.push_back(t); }
+            seg.n = k == 2 ? 0 : (seg.n > kMaxN || seg.n == p->n ? p->n : kFftMixed);
+            seg.lds_rows = std::max(seg.lds_rows, p->lds_rows);
+            seg.lds_cols = std::max(seg.lds_cols, k == 2 ? p->lds_cols : (size_t)fft_cols_raw_lds(p->n));
+        }
+        seg.n_rows = (int)rows.size() - seg.rows0;
+        seg.n_cols = (int)cols.size() - seg.cols0;
+        if (seg.n_rows) L.segs.push_back(seg);
+    }
     for (const vp_session* s : sessions) L.odd = L.odd || (s->plan->n & 1);
     for (int i = 0; i < ns; ++i) {
         const vp_plan* p = sessions[i]->plan;
@@ -100,15 +121,11 @@ vp_status group_build(SliceGroup* g, const std::vector<vp_session*>& sessions, c
             }
         };
         add(proj, lay->t_proj);
-        add(rows, p->t_rows);
-        add(cols, p->t_cols);
         add(gath, lay->t_gath);
         add(upd, lay->t_upd);
         add(vox, p->t_vox);
         add(render, p->t_render);
         L.re_proj = std::max(L.re_proj, lay->re_proj);
-        L.lds_rows = std::max(L.lds_rows, p->lds_rows);
-        L.lds_cols = std::max(L.lds_cols, p->lds_cols);
         L.re_gath = std::max(L.re_gath, lay->re_gath);
         L.lds_res = std::max(L.lds_res, lay->lds_res);
     }

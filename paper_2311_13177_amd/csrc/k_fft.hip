@@ -81,29 +81,34 @@ __device__ __forceinline__ void butterfly(float2 (&x)[R]) {
     }
 }
 
+// a / b for 0 <= a < 8192, 1 <= b <= 512 and inv = 1.0f / b: a + 1/2 is at least 1 / (2 b) away
+// from the next multiple of b, far more than the product's rounding.
+__device__ __forceinline__ int small_div(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
+
 template <int DIR, int R, bool FFAST, int E>
 __device__ __forceinline__ void stockham_stage(float2* buf, const float2* tw, int n, int count, int fstride,
-                                               int estride, int p) {
+                                               int estride, int p, int tid) {
     constexpr int MAXB = (E + R - 1) / R;  // butterflies per thread (n * count <= E * kThreads)
     const int m = n / R;
     const int total = m * count;
     const int tws = n / (p * R);
+    const float inv = 1.0f / (float)(FFAST ? count : m), pinv = 1.0f / (float)p;
     float2 x[MAXB][R];
     int bout[MAXB];
 #pragma unroll
     for (int t = 0; t < MAXB; ++t) {
-        const int idx = threadIdx.x + t * kThreads;
+        const int idx = tid + t * kThreads;
         bout[t] = -1;
         if (idx < total) {
             int f, j;
             if (FFAST) {
-                f = idx % count;
-                j = idx / count;
+                j = small_div(idx, inv);
+                f = idx - j * count;
             } else {
-                j = idx % m;
-                f = idx / m;
+                f = small_div(idx, inv);
+                j = idx - f * m;
             }
-            const int k = j % p;
+            const int k = j - small_div(j, pinv) * p;
             const int bin = f * fstride + j * estride;
             bout[t] = f * fstride + ((j - k) * R + k) * estride;
 #pragma unroll
@@ -130,15 +135,15 @@ __device__ __forceinline__ void stockham_stage(float2* buf, const float2* tw, in
 
 template <int DIR, bool FFAST, int E>
 __device__ void lds_fft(float2* buf, const float2* tw, int n, int count, int fstride, int estride, int nstage,
-                        int code) {
+                        int code, int tid) {
     int p = 1;
     for (int st = 0; st < nstage; ++st) {
         const int r = (code >> (3 * st)) & 7;
         switch (r) {
-            case 4: stockham_stage<DIR, 4, FFAST, E>(buf, tw, n, count, fstride, estride, p); break;
-            case 2: stockham_stage<DIR, 2, FFAST, E>(buf, tw, n, count, fstride, estride, p); break;
-            case 3: stockham_stage<DIR, 3, FFAST, E>(buf, tw, n, count, fstride, estride, p); break;
-            default: stockham_stage<DIR, 5, FFAST, E>(buf, tw, n, count, fstride, estride, p); break;
+            case 4: stockham_stage<DIR, 4, FFAST, E>(buf, tw, n, count, fstride, estride, p, tid); break;
+            case 2: stockham_stage<DIR, 2, FFAST, E>(buf, tw, n, count, fstride, estride, p, tid); break;
+            case 3: stockham_stage<DIR, 3, FFAST, E>(buf, tw, n, count, fstride, estride, p, tid); break;
+            default: stockham_stage<DIR, 5, FFAST, E>(buf, tw, n, count, fstride, estride, p, tid); break;
         }
         p *= r;
     }
@@ -165,7 +170,7 @@ __host__ __device__ constexpr int ct_radix(int n, int i) {
 }
 
 template <int DIR, int R, bool FFAST, int N, int COUNT, int P>
-__device__ __forceinline__ void ct_stage(float2* buf, const float2* tw) {
+__device__ __forceinline__ void ct_stage(float2* buf, const float2* tw, int tid) {
     constexpr int m = N / R, total = m * COUNT, tws = N / (P * R);
     constexpr int FS = FFAST ? 1 : N, ES = FFAST ? COUNT : 1;
     constexpr int MAXB = (total + kThreads - 1) / kThreads;
@@ -173,7 +178,7 @@ __device__ __forceinline__ void ct_stage(float2* buf, const float2* tw) {
     int bout[MAXB];
 #pragma unroll
     for (int t = 0; t < MAXB; ++t) {
-        const int idx = threadIdx.x + t * kThreads;
+        const int idx = tid + t * kThreads;
         bout[t] = -1;
         if (total % kThreads == 0 || idx < total) {
             const int f = FFAST ? idx % COUNT : idx / m;
@@ -204,56 +209,42 @@ __device__ __forceinline__ void ct_stage(float2* buf, const float2* tw) {
 }
 
 template <int DIR, bool FFAST, int N, int COUNT, int ST = 0, int P = 1>
-__device__ __forceinline__ void ct_fft(float2* buf, const float2* tw) {
+__device__ __forceinline__ void ct_fft(float2* buf, const float2* tw, int tid) {
     if constexpr (ct_radix(N, ST) != 0) {
         constexpr int R = ct_radix(N, ST);
-        ct_stage<DIR, R, FFAST, N, COUNT, P>(buf, tw);
-        ct_fft<DIR, FFAST, N, COUNT, ST + 1, P * R>(buf, tw);
+        ct_stage<DIR, R, FFAST, N, COUNT, P>(buf, tw, tid);
+        ct_fft<DIR, FFAST, N, COUNT, ST + 1, P * R>(buf, tw, tid);
     }
 }
 
-// Row transforms (count rows of length n, row-major) and column transforms (count
-// columns of length n, element j of column f at j * count + f), dispatched to the
-// compile-time variant for the common lengths.
-// NC != 0: the launch holds slices of length NC only, and its compile-time plan is the
-// whole transform (a kernel with just that variant needs far fewer registers).
+// Row transforms (count rows of length n, row-major) and column transforms (count columns
+// of length n, element j of column f at j * count + f). NC != 0: every slice of the launch has
+// length NC and its compile-time plan is the whole transform; NC = 0: runtime radices, for the
+// lengths without one. (One kernel for every length needs 170 to 250 registers, two waves per
+// SIMD; the compile-time plans up to 384 alone need 41 and 122. A batch of six slices of 128 to
+// 256: 108 us in the three passes with one kernel for all, 62 us with the two kinds apart.)
 template <int DIR, int NC = 0>
-__device__ void fft_rows_any(float2* buf, const float2* tw, int n, int nstage, int code) {
-    if constexpr (NC != 0) {
-        ct_fft<DIR, false, NC, fft_rows_per_item(NC)>(buf, tw);
-        return;
-    }
-    switch (n) {
-        case 64: ct_fft<DIR, false, 64, fft_rows_per_item(64)>(buf, tw); break;
-        case 128: ct_fft<DIR, false, 128, fft_rows_per_item(128)>(buf, tw); break;
-        case 192: ct_fft<DIR, false, 192, fft_rows_per_item(192)>(buf, tw); break;
-        case 256: ct_fft<DIR, false, 256, fft_rows_per_item(256)>(buf, tw); break;
-        case 320: ct_fft<DIR, false, 320, fft_rows_per_item(320)>(buf, tw); break;
-        case 384: ct_fft<DIR, false, 384, fft_rows_per_item(384)>(buf, tw); break;
-        case 512: ct_fft<DIR, false, 512, fft_rows_per_item(512)>(buf, tw); break;
-        default: lds_fft<DIR, false, 8>(buf, tw, n, fft_rows_per_item(n), n, 1, nstage, code); break;
-    }
+__device__ void fft_rows_any(float2* buf, const float2* tw, int n, int nstage, int code, int tid) {
+    if constexpr (NC != 0) ct_fft<DIR, false, NC, fft_rows_per_item(NC)>(buf, tw, tid);
+    else lds_fft<DIR, false, 8>(buf, tw, n, fft_rows_per_item(n), n, 1, nstage, code, tid);
 }
 template <int DIR, int NC = 0>
-__device__ void fft_cols_any(float2* buf, const float2* tw, int n, int nstage, int code) {
+__device__ void fft_cols_any(float2* buf, const float2* tw, int n, int nstage, int code, int tid) {
     if constexpr (NC != 0) {
-        ct_fft<DIR, true, NC, fft_cols_per_item(NC)>(buf, tw);
-        return;
+        ct_fft<DIR, true, NC, fft_cols_per_item(NC)>(buf, tw, tid);
+    } else {
+        const int cb = fft_cols_per_item(n);
+        lds_fft<DIR, true, 16>(buf, tw, n, cb, 1, cb, nstage, code, tid);
     }
-    switch (n) {
-        case 64: ct_fft<DIR, true, 64, fft_cols_per_item(64)>(buf, tw); break;
-        case 128: ct_fft<DIR, true, 128, fft_cols_per_item(128)>(buf, tw); break;
-        case 192: ct_fft<DIR, true, 192, fft_cols_per_item(192)>(buf, tw); break;
-        case 256: ct_fft<DIR, true, 256, fft_cols_per_item(256)>(buf, tw); break;
-        case 320: ct_fft<DIR, true, 320, fft_cols_per_item(320)>(buf, tw); break;
-        case 384: ct_fft<DIR, true, 384, fft_cols_per_item(384)>(buf, tw); break;
-        case 512: ct_fft<DIR, true, 512, fft_cols_per_item(512)>(buf, tw); break;
-        default: {
-            const int cb = fft_cols_per_item(n);
-            lds_fft<DIR, true, 16>(buf, tw, n, cb, 1, cb, nstage, code);
-            break;
-        }
-    }
+}
+
+// The thread's index, computed anew for each work item: the compiler otherwise keeps every
+// address that depends on it in a register across the items (95 to 212 registers for the column
+// passes, two to five waves per SIMD).
+__device__ __forceinline__ int item_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
 }
 
 // ------------------------------------------------------------------ row passes
@@ -263,8 +254,83 @@ __device__ void fft_cols_any(float2* buf, const float2* tw, int n, int nstage, i
 // already applied both unitary scalings).
 
 template <int DIR, int NC>
-__global__ __launch_bounds__(kThreads) void k_rows(const KArgs a) {
+__device__ __forceinline__ void rows_item(const KArgs& a, const AS4 Task* tk, int slice, int b) {
     extern __shared__ float2 sm[];
+    const int tid = item_tid();
+    const int n = NC > 0 ? NC : DF(n), nparts = DF(nparts), nstage = DF(nstage), code = DF(radix_code);
+    const size_t nn = (size_t)n * n;
+    const int fb = fft_rows_per_item(n);
+    const int r0 = tk->b, rows = min(fb, n - r0);
+    float2* A = sm;
+    float2* tw = sm + fb * n;
+    float2* img = (a.mode == COL_INVERSE || a.mode == COL_RAW_FWD) ? a.out0 + (size_t)b * nn
+                                                                     : DF(work) + (size_t)b * nparts * nn;
+    const float2* twg = DF(tw);
+    const size_t base = (size_t)r0 * n;
+    for (int i = tid; i < n; i += kThreads) tw[i] = twg[i];
+    // blade-aligned passes: grid row g holds image row (or column) g + m/2 (g < m - m/2)
+    // or g - n + m/2 (g >= n - m/2) of a centred m x m image, else zero
+    const int m = a.live_n, mh = m / 2;
+    const bool edge = m != 0 && (a.mode == COL_INVERSE || a.mode == COL_RAW_FWD);
+    if (DIR < 0 && edge) {
+        const NuEdge& ne = a.nue;
+        const size_t mm = (size_t)m * m;
+        const float2* src = ne.img_in + (size_t)b * ne.parts * mm;
+        const BladeDev bd = ne.blade[b];
+        for (int i = tid; i < fb * n; i += kThreads) {
+            const int k = i / n, g = i - k * n, gy = r0 + k;
+            const int y = gy < m - mh ? gy + mh : (gy >= n - mh ? gy - n + mh : -1);
+            const int x = g < m - mh ? g + mh : (g >= n - mh ? g - n + mh : -1);
+            float2 v = make_float2(0.f, 0.f);
+            if (k < rows && y >= 0 && x >= 0) {
+                const float2* p = src + (size_t)y * m + x;
+                if (ne.parts == 2) {
+                    if (bd.has0) v = cscale(p[0], bd.w0);
+                    if (bd.has1) v = cfma(bd.w1, p[mm], v);
+                } else {
+                    v = p[0];
+                }
+                v = cscale(v, ne.dea[x] * ne.dea[y]);
+            }
+            A[i] = v;
+        }
+    } else if (DIR < 0 && nparts == 2) {
+        const AS4 BladeDev* bd = cst(DF(blade)) + b;
+        const int has0 = bd->has0, has1 = bd->has1;
+        const float w0 = bd->w0, w1 = bd->w1;
+        const float2* p1 = img + nn;
+        for (int i = tid; i < fb * n; i += kThreads) {
+            float2 v = make_float2(0.f, 0.f);
+            if (i < rows * n) {
+                if (has0) v = cscale(img[base + i], w0);
+                if (has1) v = cfma(w1, p1[base + i], v);
+            }
+            A[i] = v;
+        }
+    } else {
+        for (int i = tid; i < fb * n; i += kThreads)
+            A[i] = i < rows * n ? img[base + i] : make_float2(0.f, 0.f);
+    }
+    __syncthreads();
+    fft_rows_any<DIR, NC>(A, tw, n, nstage, code, tid);
+    if (DIR > 0 && edge) {
+        const NuEdge& ne = a.nue;
+        float2* dst = ne.img_out + (size_t)b * ne.parts * m * m;
+        for (int i = tid; i < rows * m; i += kThreads) {
+            const int k = i / m, x = i - k * m, gy = r0 + k;
+            const int y = gy < m - mh ? gy + mh : (gy >= n - mh ? gy - n + mh : -1);
+            const int g = x < mh ? x - mh + n : x - mh;
+            if (y >= 0) dst[(size_t)y * m + x] = cscale(A[k * n + g], ne.dea[x] * ne.dea[y]);
+        }
+    } else {
+        for (int i = tid; i < rows * n; i += kThreads) img[base + i] = A[i];
+    }
+}
+
+// NC: the length of every slice of the launch (0: any length without a compile-time plan;
+// kFftMixed: any lengths up to 384 with one).
+template <int DIR, int NC>
+__global__ __launch_bounds__(kThreads) void k_rows(const KArgs a) {
     for (int ti = xcd_item(blockIdx.x, gridDim.x); ti < a.ntasks; ti += gridDim.x) {
         const AS4 Task* tk = cst(a.tasks) + ti;
         const int slice = tk->slice;
@@ -273,73 +339,17 @@ __global__ __launch_bounds__(kThreads) void k_rows(const KArgs a) {
         if (stepp && st >= DF(step_limit)) continue;
         const int b = tk->a;
         if (!active_blade(DF(schedule), DF(sched_seed), stepp, st, DF(B), b)) continue;
-        const int n = DF(n), nparts = DF(nparts), nstage = DF(nstage), code = DF(radix_code);
-        const size_t nn = (size_t)n * n;
-        const int fb = fft_rows_per_item(n);
-        const int r0 = tk->b, rows = min(fb, n - r0);
-        float2* A = sm;
-        float2* tw = sm + fb * n;
-        float2* img = (a.mode == COL_INVERSE || a.mode == COL_RAW_FWD) ? a.out0 + (size_t)b * nn
-                                                                         : DF(work) + (size_t)b * nparts * nn;
-        const float2* twg = DF(tw);
-        const size_t base = (size_t)r0 * n;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) tw[i] = twg[i];
-        // blade-aligned passes: grid row g holds image row (or column) g + m/2 (g < m - m/2)
-        // or g - n + m/2 (g >= n - m/2) of a centred m x m image, else zero
-        const int m = a.live_n, mh = m / 2;
-        const bool edge = m != 0 && (a.mode == COL_INVERSE || a.mode == COL_RAW_FWD);
-        if (DIR < 0 && edge) {
-            const NuEdge& ne = a.nue;
-            const size_t mm = (size_t)m * m;
-            const float2* src = ne.img_in + (size_t)b * ne.parts * mm;
-            const BladeDev bd = ne.blade[b];
-            for (int i = threadIdx.x; i < fb * n; i += blockDim.x) {
-                const int k = i / n, g = i - k * n, gy = r0 + k;
-                const int y = gy < m - mh ? gy + mh : (gy >= n - mh ? gy - n + mh : -1);
-                const int x = g < m - mh ? g + mh : (g >= n - mh ? g - n + mh : -1);
-                float2 v = make_float2(0.f, 0.f);
-                if (k < rows && y >= 0 && x >= 0) {
-                    const float2* p = src + (size_t)y * m + x;
-                    if (ne.parts == 2) {
-                        if (bd.has0) v = cscale(p[0], bd.w0);
-                        if (bd.has1) v = cfma(bd.w1, p[mm], v);
-                    } else {
-                        v = p[0];
-                    }
-                    v = cscale(v, ne.dea[x] * ne.dea[y]);
-                }
-                A[i] = v;
-            }
-        } else if (DIR < 0 && nparts == 2) {
-            const AS4 BladeDev* bd = cst(DF(blade)) + b;
-            const int has0 = bd->has0, has1 = bd->has1;
-            const float w0 = bd->w0, w1 = bd->w1;
-            const float2* p1 = img + nn;
-            for (int i = threadIdx.x; i < fb * n; i += blockDim.x) {
-                float2 v = make_float2(0.f, 0.f);
-                if (i < rows * n) {
-                    if (has0) v = cscale(img[base + i], w0);
-                    if (has1) v = cfma(w1, p1[base + i], v);
-                }
-                A[i] = v;
+        if constexpr (NC == kFftMixed) {
+            switch (DF(n)) {
+                case 64: rows_item<DIR, 64>(a, tk, slice, b); break;
+                case 128: rows_item<DIR, 128>(a, tk, slice, b); break;
+                case 192: rows_item<DIR, 192>(a, tk, slice, b); break;
+                case 256: rows_item<DIR, 256>(a, tk, slice, b); break;
+                case 320: rows_item<DIR, 320>(a, tk, slice, b); break;
+                default: rows_item<DIR, 384>(a, tk, slice, b); break;
             }
         } else {
-            for (int i = threadIdx.x; i < fb * n; i += blockDim.x)
-                A[i] = i < rows * n ? img[base + i] : make_float2(0.f, 0.f);
-        }
-        __syncthreads();
-        fft_rows_any<DIR, NC>(A, tw, n, nstage, code);
-        if (DIR > 0 && edge) {
-            const NuEdge& ne = a.nue;
-            float2* dst = ne.img_out + (size_t)b * ne.parts * m * m;
-            for (int i = threadIdx.x; i < rows * m; i += blockDim.x) {
-                const int k = i / m, x = i - k * m, gy = r0 + k;
-                const int y = gy < m - mh ? gy + mh : (gy >= n - mh ? gy - n + mh : -1);
-                const int g = x < mh ? x - mh + n : x - mh;
-                if (y >= 0) dst[(size_t)y * m + x] = cscale(A[k * n + g], ne.dea[x] * ne.dea[y]);
-            }
-        } else {
-            for (int i = threadIdx.x; i < rows * n; i += blockDim.x) img[base + i] = A[i];
+            rows_item<DIR, NC>(a, tk, slice, b);
         }
         __syncthreads();
     }
@@ -356,14 +366,142 @@ __global__ __launch_bounds__(kThreads) void k_rows(const KArgs a) {
 // COL_RAW_FWD: forward column DFT of caller frames, unmasked and unscaled, -> a.out0.
 
 template <int NC>
-__global__ __launch_bounds__(kThreads) void k_cols(const KArgs a) {
+__device__ __forceinline__ void cols_item(const KArgs& a, const AS4 Task* tk, int slice, int b, float* loss_part,
+                                          int n_col_items, float* red) {
     extern __shared__ float2 sm[];
-    __shared__ float red[kThreads / 64];
+    const int tid = item_tid();
     // Compile-time lengths keep each thread's measurement values and mask bytes in
     // registers (loaded with the strip, used after the forward DFT); the generic length
     // stages them in LDS beside the strip.
     constexpr bool kRegs = NC != 0;
     constexpr int kEpt = kRegs ? (NC * fft_cols_per_item(NC) + kThreads - 1) / kThreads : 1;
+    const int n = kRegs ? NC : DF(n);
+    const int nparts = DF(nparts), nstage = DF(nstage), code = DF(radix_code);
+    const size_t nn = (size_t)n * n;
+    const int cb = fft_cols_per_item(n), lcb = cb == 16 ? 4 : (cb == 8 ? 3 : 2);  // 4, 8 or 16
+    const int c0 = tk->b * cb, cols = min(cb, n - c0);
+    const int ne = n * cb;
+    // LDS: the strip (cb columns of n) and the twiddles (plus, for the generic length,
+    // the strip's measurement and mask), all loaded in one pass so that their
+    // latencies overlap
+    float2* A = sm;
+    float2* tw = sm + cb * n;
+    float2* Y = tw + n;
+    uint8_t* M = reinterpret_cast<uint8_t*>(Y + cb * n);
+    float2 yr[kEpt];
+    uint8_t mr[kEpt];
+    float2* img = DF(work) + (size_t)b * nparts * nn;
+    const float2* twg = DF(tw);
+    const bool raw = a.mode == COL_INVERSE || a.mode == COL_RAW_FWD;
+    const bool from_in = a.mode == COL_ADJOINT || raw;
+    const float2* src = from_in ? a.in0 + (size_t)b * nn : img;
+    float2* dst = raw ? a.out0 + (size_t)b * nn : img;
+    const uint8_t* mk = DF(mask) + (size_t)b * nn;
+    const float2* yy = DF(y);
+    const float2* yb = (yy && !from_in) ? yy + (size_t)b * nn : nullptr;
+    // rows of a centred image of size live_n (all rows when 0)
+    const int lv = raw ? a.live_n : 0, lv_lo = lv - lv / 2, lv_hi = n - lv / 2;
+    for (int i = tid; i < n; i += kThreads) tw[i] = twg[i];
+    auto load = [&](int i, float2& w, uint8_t& m) {
+        const int y = i >> lcb, c = i & (cb - 1);
+        float2 v = make_float2(0.f, 0.f);
+        w = v;
+        m = 0;
+        if (c < cols) {
+            const size_t gi = (size_t)y * n + c0 + c;
+            if (raw) {
+                // a raw forward pass of a centred image reads only its rows
+                if (a.mode == COL_INVERSE || lv == 0 || y < lv_lo || y >= lv_hi) v = src[gi];
+            } else {
+                v = src[gi];
+                m = mk[gi];
+                if (yb) w = yb[gi];
+            }
+        }
+        A[i] = v;
+    };
+    if constexpr (kRegs) {
+#pragma unroll
+        for (int k = 0; k < kEpt; ++k) {
+            const int i = tid + k * kThreads;
+            yr[k] = make_float2(0.f, 0.f);
+            mr[k] = 0;
+            if (kEpt * kThreads == NC * fft_cols_per_item(NC) || i < ne) load(i, yr[k], mr[k]);
+        }
+    } else {
+        for (int i = tid; i < ne; i += kThreads) {
+            float2 w;
+            uint8_t m;
+            load(i, w, m);
+            if (!raw) {
+                Y[i] = w;
+                M[i] = m;
+            }
+        }
+    }
+    __syncthreads();
+    if (!from_in || a.mode == COL_RAW_FWD) fft_cols_any<-1, NC>(A, tw, n, nstage, code, tid);
+    const float sc = 1.0f / (float)n;
+    // the step's residual and loss carry the data-term weight
+    const float dw = a.mode == COL_STEP ? DF(data_w) : 1.0f;
+    const float sc_res = dw * sc;
+    float lsum = 0.f;
+    auto mask_res = [&](int i, float2 yv, uint8_t mv) {
+        const int y = i >> lcb, c = i & (cb - 1);
+        float2 v = make_float2(0.f, 0.f);
+        if (c < cols) {
+            const bool on = mv != 0;
+            const float2 x = A[i];
+            if (a.mode == COL_ADJOINT) {
+                if (on) v = cscale(x, sc);
+            } else {
+                float2 r = make_float2(0.f, 0.f);
+                if (on) r = csub(cscale(x, sc), yv);
+                if (a.mode == COL_FORWARD) {
+                    a.out0[(size_t)b * nn + (size_t)y * n + c0 + c] = r;
+                } else {
+                    lsum = __builtin_fmaf(r.x, r.x, lsum);
+                    lsum = __builtin_fmaf(r.y, r.y, lsum);
+                    v = cscale(r, sc_res);
+                }
+            }
+        }
+        A[i] = v;
+    };
+    if (!raw) {
+        if constexpr (kRegs) {
+#pragma unroll
+            for (int k = 0; k < kEpt; ++k) {
+                const int i = tid + k * kThreads;
+                if (kEpt * kThreads == NC * fft_cols_per_item(NC) || i < ne) mask_res(i, yr[k], mr[k]);
+            }
+        } else {
+            for (int i = tid; i < ne; i += kThreads) mask_res(i, Y[i], M[i]);
+        }
+    }
+    __syncthreads();
+    if (a.mode != COL_FORWARD) {
+        if (a.mode != COL_RAW_FWD) fft_cols_any<1, NC>(A, tw, n, nstage, code, tid);
+        // a raw inverse pass feeding a centred crop writes only its rows
+        const bool all = a.mode != COL_INVERSE || lv == 0;
+        for (int i = tid; i < ne; i += kThreads) {
+            const int y = i >> lcb, c = i & (cb - 1);
+            if (c < cols && (all || y < lv_lo || y >= lv_hi)) dst[(size_t)y * n + c0 + c] = A[i];
+        }
+    }
+    if (a.mode == COL_STEP) {
+        // loss partial: butterfly sum within each wave, then the four wave sums in order
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+        if ((tid & 63) == 0) red[tid >> 6] = lsum;
+        __syncthreads();
+        if (tid == 0) loss_part[b * n_col_items + tk->b] = dw * ((red[0] + red[1]) + (red[2] + red[3]));
+    }
+}
+
+template <int NC>
+__global__ __launch_bounds__(kThreads) void k_cols(const KArgs a) {
+    __shared__ float red[kThreads / 64];
     for (int ti = xcd_item(blockIdx.x, gridDim.x); ti < a.ntasks; ti += gridDim.x) {
         const AS4 Task* tk = cst(a.tasks) + ti;
         const int slice = tk->slice;
@@ -377,127 +515,17 @@ __global__ __launch_bounds__(kThreads) void k_cols(const KArgs a) {
             if (a.mode == COL_STEP && threadIdx.x == 0) loss_part[b * n_col_items + tk->b] = 0.f;
             continue;
         }
-        const int n = kRegs ? NC : DF(n);
-        const int nparts = DF(nparts), nstage = DF(nstage), code = DF(radix_code);
-        const size_t nn = (size_t)n * n;
-        const int cb = fft_cols_per_item(n);
-        const int c0 = tk->b * cb, cols = min(cb, n - c0);
-        const int ne = n * cb;
-        // LDS: the strip (cb columns of n) and the twiddles (plus, for the generic length,
-        // the strip's measurement and mask), all loaded in one pass so that their
-        // latencies overlap
-        float2* A = sm;
-        float2* tw = sm + cb * n;
-        float2* Y = tw + n;
-        uint8_t* M = reinterpret_cast<uint8_t*>(Y + cb * n);
-        float2 yr[kEpt];
-        uint8_t mr[kEpt];
-        float2* img = DF(work) + (size_t)b * nparts * nn;
-        const float2* twg = DF(tw);
-        const bool raw = a.mode == COL_INVERSE || a.mode == COL_RAW_FWD;
-        const bool from_in = a.mode == COL_ADJOINT || raw;
-        const float2* src = from_in ? a.in0 + (size_t)b * nn : img;
-        float2* dst = raw ? a.out0 + (size_t)b * nn : img;
-        const uint8_t* mk = DF(mask) + (size_t)b * nn;
-        const float2* yy = DF(y);
-        const float2* yb = (yy && !from_in) ? yy + (size_t)b * nn : nullptr;
-        // rows of a centred image of size live_n (all rows when 0)
-        const int lv = raw ? a.live_n : 0, lv_lo = lv - lv / 2, lv_hi = n - lv / 2;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) tw[i] = twg[i];
-        auto load = [&](int i, float2& w, uint8_t& m) {
-            const int y = i / cb, c = i - (i / cb) * cb;
-            float2 v = make_float2(0.f, 0.f);
-            w = v;
-            m = 0;
-            if (c < cols) {
-                const size_t gi = (size_t)y * n + c0 + c;
-                if (raw) {
-                    // a raw forward pass of a centred image reads only its rows
-                    if (a.mode == COL_INVERSE || lv == 0 || y < lv_lo || y >= lv_hi) v = src[gi];
-                } else {
-                    v = src[gi];
-                    m = mk[gi];
-                    if (yb) w = yb[gi];
-                }
-            }
-            A[i] = v;
-        };
-        if constexpr (kRegs) {
-#pragma unroll
-            for (int k = 0; k < kEpt; ++k) {
-                const int i = threadIdx.x + k * kThreads;
-                yr[k] = make_float2(0.f, 0.f);
-                mr[k] = 0;
-                if (kEpt * kThreads == NC * fft_cols_per_item(NC) || i < ne) load(i, yr[k], mr[k]);
+        if constexpr (NC == kFftMixed) {
+            switch (DF(n)) {
+                case 64: cols_item<64>(a, tk, slice, b, loss_part, n_col_items, red); break;
+                case 128: cols_item<128>(a, tk, slice, b, loss_part, n_col_items, red); break;
+                case 192: cols_item<192>(a, tk, slice, b, loss_part, n_col_items, red); break;
+                case 256: cols_item<256>(a, tk, slice, b, loss_part, n_col_items, red); break;
+                case 320: cols_item<320>(a, tk, slice, b, loss_part, n_col_items, red); break;
+                default: cols_item<384>(a, tk, slice, b, loss_part, n_col_items, red); break;
             }
         } else {
-            for (int i = threadIdx.x; i < ne; i += blockDim.x) {
-                float2 w;
-                uint8_t m;
-                load(i, w, m);
-                if (!raw) {
-                    Y[i] = w;
-                    M[i] = m;
-                }
-            }
-        }
-        __syncthreads();
-        if (!from_in || a.mode == COL_RAW_FWD) fft_cols_any<-1, NC>(A, tw, n, nstage, code);
-        const float sc = 1.0f / (float)n;
-        // the step's residual and loss carry the data-term weight
-        const float dw = a.mode == COL_STEP ? DF(data_w) : 1.0f;
-        const float sc_res = dw * sc;
-        float lsum = 0.f;
-        auto mask_res = [&](int i, float2 yv, uint8_t mv) {
-            const int y = i / cb, c = i - (i / cb) * cb;
-            float2 v = make_float2(0.f, 0.f);
-            if (c < cols) {
-                const bool on = mv != 0;
-                const float2 x = A[i];
-                if (a.mode == COL_ADJOINT) {
-                    if (on) v = cscale(x, sc);
-                } else {
-                    float2 r = make_float2(0.f, 0.f);
-                    if (on) r = csub(cscale(x, sc), yv);
-                    if (a.mode == COL_FORWARD) {
-                        a.out0[(size_t)b * nn + (size_t)y * n + c0 + c] = r;
-                    } else {
-                        lsum = __builtin_fmaf(r.x, r.x, lsum);
-                        lsum = __builtin_fmaf(r.y, r.y, lsum);
-                        v = cscale(r, sc_res);
-                    }
-                }
-            }
-            A[i] = v;
-        };
-        if (!raw) {
-            if constexpr (kRegs) {
-#pragma unroll
-                for (int k = 0; k < kEpt; ++k) {
-                    const int i = threadIdx.x + k * kThreads;
-                    if (kEpt * kThreads == NC * fft_cols_per_item(NC) || i < ne) mask_res(i, yr[k], mr[k]);
-                }
-            } else {
-                for (int i = threadIdx.x; i < ne; i += blockDim.x) mask_res(i, Y[i], M[i]);
-            }
-        }
-        __syncthreads();
-        if (a.mode != COL_FORWARD) {
-            if (a.mode != COL_RAW_FWD) fft_cols_any<1, NC>(A, tw, n, nstage, code);
-            // a raw inverse pass feeding a centred crop writes only its rows
-            const bool all = a.mode != COL_INVERSE || lv == 0;
-            for (int i = threadIdx.x; i < ne; i += blockDim.x) {
-                const int y = i / cb, c = i - (i / cb) * cb;
-                if (c < cols && (all || y < lv_lo || y >= lv_hi)) dst[(size_t)y * n + c0 + c] = A[i];
-            }
-        }
-        if (a.mode == COL_STEP) {
-            // loss partial: butterfly sum within each wave, then the four wave sums in order
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
-            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = lsum;
-            __syncthreads();
-            if (threadIdx.x == 0) loss_part[b * n_col_items + tk->b] = dw * ((red[0] + red[1]) + (red[2] + red[3]));
+            cols_item<NC>(a, tk, slice, b, loss_part, n_col_items, red);
         }
         __syncthreads();
     }
@@ -507,7 +535,9 @@ __global__ __launch_bounds__(kThreads) void k_cols(const KArgs a) {
 
 static inline int grid_for(int ntasks) { return ntasks < 1 ? 1 : (ntasks > (1 << 20) ? (1 << 20) : ntasks); }
 
-// n: the common length of every slice of the launch (0 if they differ).
+bool fft_compiled(int n) { return n == 64 || n == 128 || n == 192 || n == 256 || n == 320 || n == 384 || n == 512; }
+
+// n: the length of every slice of the launch, or kFftMixed.
 hipError_t launch_rows(const KArgs& a, int dir, int n, size_t lds, hipStream_t s) {
     if (a.ntasks <= 0) return hipSuccess;
     const dim3 g(grid_for(a.ntasks)), b(kThreads);
@@ -518,6 +548,10 @@ hipError_t launch_rows(const KArgs& a, int dir, int n, size_t lds, hipStream_t s
         break
     switch (n) {
         RV(64); RV(128); RV(192); RV(256); RV(320); RV(384); RV(512);
+        case kFftMixed:
+            if (dir < 0) hipLaunchKernelGGL((k_rows<-1, kFftMixed>), g, b, lds, s, a);
+            else hipLaunchKernelGGL((k_rows<1, kFftMixed>), g, b, lds, s, a);
+            break;
         default: RV(0);
     }
 #undef RV
@@ -528,14 +562,14 @@ hipError_t launch_cols(const KArgs& a, int n, size_t lds, hipStream_t s) {
     const dim3 g(grid_for(a.ntasks)), b(kThreads);
     // the compile-time lengths hold the measurement and mask in registers: LDS for the
     // strip and the twiddles only
-    if (n == 64 || n == 128 || n == 192 || n == 256 || n == 320 || n == 384 || n == 512)
-        lds = (size_t)fft_cols_raw_lds(n);
+    if (fft_compiled(n)) lds = (size_t)fft_cols_raw_lds(n);
 #define CV(N)                                                  \
     case N:                                                    \
         hipLaunchKernelGGL((k_cols<N>), g, b, lds, s, a);      \
         break
     switch (n) {
         CV(64); CV(128); CV(192); CV(256); CV(320); CV(384); CV(512);
+        case kFftMixed: hipLaunchKernelGGL((k_cols<kFftMixed>), g, b, lds, s, a); break;
         default: CV(0);
     }
 #undef CV

@@ -150,7 +150,6 @@ __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, float2 v, int v
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2, v), r, voff, soff, CP);
 }
 
-using f32x4 = float __attribute__((ext_vector_type(4)));
 // ------------------------------------------------------------------ LDS staging
 //
 // A rectangular region (rows x cols) of an n x n image, origin (gy0, gx0), is staged

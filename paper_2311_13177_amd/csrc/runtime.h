@@ -14,9 +14,11 @@ namespace vp {
 // waves: 4 or 8 per work item (the layout's proj_w: its groups hold waves * gw parts)
 // odd: whether any slice of the launch has an odd n
 hipError_t launch_project(const KArgs& a, int rows, int gw, int waves, int re, bool odd, hipStream_t s);
-// n: the common length of every slice of the launch (0 if they differ).
+// n: the length of every slice of the launch, or kFftMixed (lds: the largest over the slices).
 hipError_t launch_rows(const KArgs& a, int dir, int n, size_t lds, hipStream_t s);
 hipError_t launch_cols(const KArgs& a, int n, size_t lds, hipStream_t s);
+// Whether a length has compile-time passes.
+bool fft_compiled(int n);
 // waves: 4 or 8 per work item (the layout's gath_w: its bin chunks hold waves * sc bins)
 hipError_t launch_gather(const KArgs& a, int mode, int rows, int sc, int waves, int re, hipStream_t s);
 // The resident-parts gather: lds bytes of the largest knot's parts (Layout::lds_res).
@@ -31,6 +33,14 @@ hipError_t launch_baseline_avg(const uint8_t* mask, const float2* y, float2* out
 hipError_t launch_psnr(const float2* img, const float2* truth, long long npx, int n_images, double* terms,
                        hipStream_t s);
 
+// The row and column passes of a launch over slices of several lengths: items [rows0, rows0 +
+// n_rows) and [cols0, cols0 + n_cols) have length n (kFftMixed: several of the lengths up to 384
+// with a compile-time plan; 0: any without one).
+struct FftSegment {
+    int n = 0, rows0 = 0, n_rows = 0, cols0 = 0, n_cols = 0;
+    size_t lds_rows = 0, lds_cols = 0;
+};
+
 // Device work lists of one optimiser step and the dynamic LDS of each stage.
 struct StageLists {
     const Task* proj = nullptr;
@@ -44,8 +54,9 @@ struct StageLists {
     int n_proj = 0, n_rows = 0, n_cols = 0, n_gath = 0, n_vox = 0, n_render = 0, n_upd = 0;
     Tiles tiles;
     bool odd = false;  // whether any slice has an odd n
-    int fft_n = 0;  // common length of every slice (0 if they differ)
+    int fft_n = 0;  // length of the slice (of a group's first)
     size_t lds_rows = 0, lds_cols = 0;
+    std::vector<FftSegment> segs;  // a group's lengths (empty: one slice)
     int re_proj = 0, re_gath = 0;  // largest staged regions (elements)
     size_t lds_res = 0;            // resident-parts gather: LDS bytes of the largest knot
     int epi = EPI_GENERIC;         // optimiser epilogue every slice of the step can take

@@ -211,14 +211,25 @@ void launch_step(const KArgs& base, const StageLists& L, hipStream_t s, hipError
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, s)) != hipSuccess) { *err = e; return; }
     a.snap = 0;
     MARK(1);
-    a.tasks = L.rows; a.ntasks = L.n_rows;
-    if ((e = launch_rows(a, -1, L.fft_n, L.lds_rows, s)) != hipSuccess) { *err = e; return; }
+    const FftSegment one{L.fft_n, 0, L.n_rows, 0, L.n_cols, L.lds_rows, L.lds_cols};
+    const FftSegment* segs = L.segs.empty() ? &one : L.segs.data();
+    const int nseg = L.segs.empty() ? 1 : (int)L.segs.size();
+    auto rows = [&](int dir) {
+        for (int i = 0; i < nseg; ++i) {
+            a.tasks = L.rows + segs[i].rows0; a.ntasks = segs[i].n_rows;
+            if ((e = launch_rows(a, dir, segs[i].n, segs[i].lds_rows, s)) != hipSuccess) return false;
+        }
+        return true;
+    };
+    if (!rows(-1)) { *err = e; return; }
     MARK(2);
-    a.tasks = L.cols; a.ntasks = L.n_cols; a.mode = COL_STEP;
-    if ((e = launch_cols(a, L.fft_n, L.lds_cols, s)) != hipSuccess) { *err = e; return; }
+    a.mode = COL_STEP;
+    for (int i = 0; i < nseg; ++i) {
+        a.tasks = L.cols + segs[i].cols0; a.ntasks = segs[i].n_cols;
+        if ((e = launch_cols(a, segs[i].n, segs[i].lds_cols, s)) != hipSuccess) { *err = e; return; }
+    }
     MARK(3);
-    a.tasks = L.rows; a.ntasks = L.n_rows;
-    if ((e = launch_rows(a, 1, L.fft_n, L.lds_rows, s)) != hipSuccess) { *err = e; return; }
+    if (!rows(1)) { *err = e; return; }
     MARK(4);
     a.tasks = L.gath; a.ntasks = L.n_gath;
     a.snap = 1;

@@ -77,6 +77,8 @@ __host__ __device__ constexpr int fft_rows_per_item(int n) { return 1024 / n < 1
 __host__ __device__ constexpr int fft_cols_per_item(int n) {
     return n == 512 ? 8 : (n > 256 ? 4 : (n == 256 || n == 192 ? 8 : 16));
 }
+// Length argument of a DFT pass over several of the lengths up to 384 with a compile-time plan.
+constexpr int kFftMixed = -1;
 // LDS of a column item without the measurement and mask strips (the raw passes)
 __host__ __device__ constexpr int fft_cols_raw_lds(int n) { return (fft_cols_per_item(n) * n + n) * 8; }
 
