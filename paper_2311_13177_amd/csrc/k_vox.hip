@@ -1,51 +1,76 @@
 // Voxel-wise kernels: operator TV/L1 gradient, objective regulariser terms and the
 // renders (Section 4.3, Section 6 fat/water split).
 
+#include <algorithm>
+
 #include "kcommon.h"
 
 namespace vp {
 
-// tv_w * grad TV + l1_w * grad L1 at voxel (t, s, y, x) of a [T][S][n][n] volume.
-__device__ __forceinline__ float2 reg_grad(const float2* __restrict__ V, size_t idx, int t, int s, int y, int x,
-                                           int n, int S, int T, float tv_w, float l1_w, float eps) {
-    const float eps2 = charb_eps2(eps);
-    const float2 v0 = V[idx];
-    float2 g = make_float2(0.f, 0.f);
-    if (tv_w != 0.f) {
-        const size_t nn = (size_t)n * n;
-        if (t > 0) g = cadd(g, charb_w(csub(v0, V[idx - (size_t)S * nn]), eps2));
-        if (t + 1 < T) g = csub(g, charb_w(csub(V[idx + (size_t)S * nn], v0), eps2));
-        if (s > 0) g = cadd(g, charb_w(csub(v0, V[idx - nn]), eps2));
-        if (s + 1 < S) g = csub(g, charb_w(csub(V[idx + nn], v0), eps2));
-        if (y > 0) g = cadd(g, charb_w(csub(v0, V[idx - n]), eps2));
-        if (y + 1 < n) g = csub(g, charb_w(csub(V[idx + n], v0), eps2));
-        if (x > 0) g = cadd(g, charb_w(csub(v0, V[idx - 1]), eps2));
-        if (x + 1 < n) g = csub(g, charb_w(csub(V[idx + 1], v0), eps2));
-        g = cscale(g, tv_w);
-    }
-    if (l1_w != 0.f) g = cfma(l1_w, charb_w(v0, eps2), g);
-    return g;
-}
+// a / b for integers with (float)(a + 1) exact and a quotient below 2^13, inv = 1.0f / b: a + 1/2
+// is at least 1 / (2 b) away from the next multiple of b, more than the product's rounding.
+__device__ __forceinline__ int small_div(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
 
 // ------------------------------------------------------------------ voxel-wise kernels
 
 // Operator TV/L1 gradient: grad (+)= tv_w grad TV + l1_w grad L1 (weights from the descriptor).
-__global__ __launch_bounds__(kThreads) void k_tv_grad(const KArgs a) {
-    for (int ti = blockIdx.x; ti < a.ntasks; ti += gridDim.x) {
-        const AS4 Task* tk = cst(a.tasks) + ti;
-        const int slice = tk->slice;
-        const int n = DF(n), S = DF(S), T = DF(T);
-        const float tv_w = DF(tv_w), l1_w = DF(l1_w), teps = DF(tv_eps);
-        const float2* V = DF(vol[0]);
-        float2* grad = DF(grad);
-        const size_t nvox = (size_t)T * S * n * n;
-        const size_t i0 = (size_t)tk->a * kVoxItem;
-        for (size_t i = i0 + threadIdx.x; i < min(nvox, i0 + kVoxItem); i += blockDim.x) {
-            const int x = (int)(i % n), y = (int)((i / n) % n), s = (int)((i / ((size_t)n * n)) % S);
-            const int t = (int)(i / ((size_t)S * n * n));
-            float2 g = reg_grad(V, i, t, s, y, x, n, S, T, tv_w, l1_w, teps);
-            if (a.accumulate) g = cadd(grad[i], g);
-            grad[i] = g;
+// A block takes kTvPx pixels of one bin's plane (blockIdx.y = knot * S + bin), the planes and rows
+// around them served by the caches; all loads of a thread's pixels are issued before any is used
+// (a missing neighbour reads the pixel itself and is not added). It is bound by those cache
+// loads; with a 64-bit division per coordinate of every voxel it was bound by them instead
+// (150^2 x 12 bins x 5 knots: 49 us, now 11.6 us).
+constexpr int kTvPer = 2;
+constexpr int kTvPx = kTvPer * kThreads;
+__global__ __launch_bounds__(kThreads) void k_tv_grad(const float2* __restrict__ V, float2* __restrict__ grad, int n,
+                                                      int S, int T, float tv_w, float l1_w, float teps, int accumulate) {
+    const float eps2 = charb_eps2(teps), ninv = 1.0f / (float)n;
+    const int nn = n * n;
+    const bool tv = tv_w != 0.f, l1 = l1_w != 0.f;
+    for (int plane = blockIdx.y; plane < S * T; plane += gridDim.y) {
+        const int t = plane / S, s = plane - t * S;
+        const size_t p0 = (size_t)plane * nn;
+        float2 v0[kTvPer], nb[kTvPer][8], old[kTvPer];
+        int px[kTvPer], xx[kTvPer], yy[kTvPer];
+#pragma unroll
+        for (int k = 0; k < kTvPer; ++k) {
+            const int p = blockIdx.x * kTvPx + k * kThreads + threadIdx.x;
+            px[k] = p;
+            const int q = min(p, nn - 1);
+            const int y = small_div(q, ninv), x = q - y * n;
+            xx[k] = x;
+            yy[k] = y;
+            const size_t i = p0 + q;
+            v0[k] = V[i];
+            if (tv) {
+                nb[k][0] = V[t > 0 ? i - (size_t)S * nn : i];
+                nb[k][1] = V[t + 1 < T ? i + (size_t)S * nn : i];
+                nb[k][2] = V[s > 0 ? i - nn : i];
+                nb[k][3] = V[s + 1 < S ? i + nn : i];
+                nb[k][4] = V[y > 0 ? i - n : i];
+                nb[k][5] = V[y + 1 < n ? i + n : i];
+                nb[k][6] = V[x > 0 ? i - 1 : i];
+                nb[k][7] = V[x + 1 < n ? i + 1 : i];
+            }
+            if (accumulate) old[k] = grad[i];
+        }
+#pragma unroll
+        for (int k = 0; k < kTvPer; ++k) {
+            if (px[k] >= nn) continue;
+            float2 g = make_float2(0.f, 0.f);
+            if (tv) {
+                if (t > 0) g = cadd(g, charb_w(csub(v0[k], nb[k][0]), eps2));
+                if (t + 1 < T) g = csub(g, charb_w(csub(nb[k][1], v0[k]), eps2));
+                if (s > 0) g = cadd(g, charb_w(csub(v0[k], nb[k][2]), eps2));
+                if (s + 1 < S) g = csub(g, charb_w(csub(nb[k][3], v0[k]), eps2));
+                if (yy[k] > 0) g = cadd(g, charb_w(csub(v0[k], nb[k][4]), eps2));
+                if (yy[k] + 1 < n) g = csub(g, charb_w(csub(nb[k][5], v0[k]), eps2));
+                if (xx[k] > 0) g = cadd(g, charb_w(csub(v0[k], nb[k][6]), eps2));
+                if (xx[k] + 1 < n) g = csub(g, charb_w(csub(nb[k][7], v0[k]), eps2));
+                g = cscale(g, tv_w);
+            }
+            if (l1) g = cfma(l1_w, charb_w(v0[k], eps2), g);
+            if (accumulate) g = cadd(old[k], g);
+            grad[p0 + px[k]] = g;
         }
     }
 }
@@ -66,9 +91,16 @@ __global__ __launch_bounds__(kThreads) void k_reg_value(const KArgs a) {
         const float2* V = stepp ? DF(vol[st & 1]) : DF(vol[0]);
         const float e = DF(tv_eps), e2 = e * e;
         double tv = 0.0, l1 = 0.0;
-        for (size_t i = i0 + threadIdx.x; i < min(nvox, i0 + kVoxItem); i += blockDim.x) {
-            const int x = (int)(i % n), y = (int)((i / n) % n), s = (int)((i / nn) % S);
-            const int t = (int)(i / ((size_t)S * nn));
+        // the item's first plane (knot * S + bin) and offset in it; a voxel's plane, row and column
+        // follow by 32-bit arithmetic
+        const int q0 = (int)(i0 / nn), r0 = (int)(i0 - (size_t)q0 * nn);
+        const float nninv = 1.0f / (float)(n * n), ninv = 1.0f / (float)n;
+        const int cnt = (int)min(nvox - i0, (size_t)kVoxItem);
+        for (int j = threadIdx.x; j < cnt; j += kThreads) {
+            const size_t i = i0 + j;
+            const int dq = small_div(r0 + j, nninv), p = r0 + j - dq * (n * n);
+            const int y = small_div(p, ninv), x = p - y * n;
+            const int t = (q0 + dq) / S, s = q0 + dq - t * S;
             const float2 v0 = V[i];
             float part = 0.f;
             auto term = [&](float2 z) {
@@ -130,8 +162,10 @@ __global__ __launch_bounds__(kThreads) void k_render(const KArgs a) {
 static inline int grid_for(int ntasks) { return ntasks < 1 ? 1 : (ntasks > (1 << 20) ? (1 << 20) : ntasks); }
 
 hipError_t launch_tv_grad(const KArgs& a, hipStream_t s) {
-    if (a.ntasks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tv_grad, dim3(grid_for(a.ntasks)), dim3(kThreads), 0, s, a);
+    const SliceDesc& d = a.one;
+    const dim3 g((unsigned)((d.n * d.n + kTvPx - 1) / kTvPx), (unsigned)std::min(d.S * d.T, 65535));
+    hipLaunchKernelGGL(k_tv_grad, g, dim3(kThreads), 0, s, d.vol[0], d.grad, d.n, d.S, d.T, d.tv_w, d.l1_w, d.tv_eps,
+                       a.accumulate);
     return hipGetLastError();
 }
 hipError_t launch_reg_value(const KArgs& a, hipStream_t s) {

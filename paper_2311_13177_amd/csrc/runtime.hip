@@ -950,8 +950,6 @@ extern "C" vp_status vp_tv_grad(const vp_plan* p, const vp_c64* d_vol, float tv_
     a.one.l1_w = l1_w;
     a.one.tv_eps = eps;
     a.accumulate = accumulate != 0;
-    a.tasks = sc.t->t_vox;
-    a.ntasks = (int)p->t_vox.size();
     hipError_t e = launch_tv_grad(a, sc.s);
     return hip_status(e, "vp_tv_grad");
 }
