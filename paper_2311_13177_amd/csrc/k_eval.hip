@@ -63,17 +63,19 @@ __global__ __launch_bounds__(kThreads) void k_baseline_avg(const uint8_t* __rest
         out[(size_t)blockIdx.y * nn + px + v] = cscale(acc[v], 1.0f / ((float)max(c[v], 1) * (float)n));
 }
 
-// Square root of x >= 0 in FP64: the hardware's FP32 reciprocal square root (about 1 ulp) and one
-// Newton step in FP64, within 1e-14 relative, a third of the library's instructions (which bound
-// k_psnr: one CU works on an image); values whose square leaves FP32's normal range take the
-// library's.
+// Square root of x >= 0 in FP64: the hardware's FP32 reciprocal square root (about 1 ulp), then a
+// Newton step (1e-14 relative) and a correction by the exact residual in FP64, which
+// leaves all but one value in 30000 correctly rounded, with half the library root's instructions
+// (they bound k_psnr: one CU works on an image).
+// Values outside FP32's normal range take the library's.
 __device__ __forceinline__ double sqrt64(double x) {
     if (x == 0.0) return 0.0;
     const float xf = (float)x;
     if (!(xf >= 1.1754944e-38f && xf <= 3.4028235e38f)) return sqrt(x);
     const double y = (double)__builtin_amdgcn_rsqf(xf);
     const double h = 0.5 * y, g = x * y;
-    return fma(g, fma(-h, g, 0.5), g);
+    const double s = fma(g, fma(-h, g, 0.5), g);
+    return fma(fma(-s, s, x), h, s);
 }
 
 // One block per image of npx samples: FP64 sum of (|image| - |truth|)^2 and the peak
