@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
                 }
             }
         } else {
-            update_and_finish<SCM, PPT, EPI, kPre>(a, slice, stepp, st, acc, pm, pv, kt, y0, x0, lane, sw, ns);
+            update_and_finish<SCM, PPT, EPI, kPre>(a, slice, st, acc, pm, pv, kt, y0, x0, lane, sw, ns);
         }
     }
 }
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kThreads) void k_update(const KArgs a) {
         const AS4 Task* tk = cst(a.tasks) + ti;
         const int slice = tk->slice;
         int* const stepp = DF(step);
-        const int st = read_step_at(stepp, a.snap);
+        const int st = stepp ? read_step_at(stepp, a.snap) : a.step0;
         if (stepp && st >= DF(step_limit)) continue;
         const int n = DF(n), S = DF(S);
         const int kt = tk->a;
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kThreads) void k_update(const KArgs a) {
         float2 acc[SC][1];
 #pragma unroll
         for (int q = 0; q < SC; ++q) acc[q][0] = G[(size_t)min(sw + q, S - 1) * nn + off];
-        update_and_finish<SC, 1, EPI, false>(a, slice, stepp, st, acc, acc, acc, kt, y, x0, lane, sw, ns);
+        update_and_finish<SC, 1, EPI, false>(a, slice, st, acc, acc, acc, kt, y, x0, lane, sw, ns);
     }
 }
 

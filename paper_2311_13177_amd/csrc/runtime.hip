@@ -20,9 +20,79 @@ namespace vp {
 // ------------------------------------------------------------------ device tables
 
 DeviceLayout::~DeviceLayout() {
-    void* ptrs[] = {groups, t_proj, t_gath, t_upd};
-    for (void* p : ptrs)
-        if (p) (void)hipFree(p);
+    if (base) (void)hipFree(base);
+}
+
+WorkspaceSlots::~WorkspaceSlots() {
+    for (Slot& w : slot) {
+        if (!w.ptr) continue;
+        (void)hipEventSynchronize(w.done);
+        (void)hipFree(w.ptr);
+        (void)hipEventDestroy(w.done);
+    }
+}
+
+hipError_t Workspace::take(WorkspaceSlots* slots, size_t bytes, hipStream_t stream) {
+    s = stream;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    bool keep = bytes <= WorkspaceSlots::kKeepBytes && s != hipStreamPerThread;
+    if (keep && (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) {
+        (void)hipGetLastError();
+        keep = false;
+    }
+    if (keep) {
+        std::lock_guard<std::mutex> lk(slots->mu);
+        int fresh = -1;
+        for (int i = 0; i < WorkspaceSlots::kSlots; ++i) {
+            WorkspaceSlots::Slot& w = slots->slot[i];
+            if (!w.ptr && !w.busy) fresh = i;
+            if (!w.ptr || w.busy || w.stream != s || w.bytes < bytes) continue;
+            if (hipStreamWaitEvent(s, w.done, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                continue;
+            }
+            w.busy = true;
+            from = slots;
+            slot = i;
+            ptr = w.ptr;
+            return hipSuccess;
+        }
+        if (fresh >= 0) {
+            WorkspaceSlots::Slot& w = slots->slot[fresh];
+            if (hipEventCreateWithFlags(&w.done, hipEventDisableTiming) == hipSuccess) {
+                const hipError_t e = hipMallocAsync(&ptr, bytes, s);
+                if (e != hipSuccess) {
+                    (void)hipEventDestroy(w.done);
+                    return e;
+                }
+                w.ptr = ptr;
+                w.bytes = bytes;
+                w.stream = s;
+                w.busy = true;
+                from = slots;
+                slot = fresh;
+                return hipSuccess;
+            }
+            (void)hipGetLastError();
+        }
+    }
+    return hipMallocAsync(&ptr, bytes, s);
+}
+
+Workspace::~Workspace() {
+    if (!ptr) return;
+    if (!from) {
+        (void)hipFreeAsync(ptr, s);
+        return;
+    }
+    std::lock_guard<std::mutex> lk(from->mu);
+    WorkspaceSlots::Slot& w = from->slot[slot];
+    w.busy = false;
+    if (hipEventRecord(w.done, s) == hipSuccess) return;
+    (void)hipGetLastError();
+    (void)hipFreeAsync(ptr, s);
+    (void)hipEventDestroy(w.done);
+    w.ptr = nullptr;
 }
 
 DeviceTables::~DeviceTables() {
@@ -30,10 +100,8 @@ DeviceTables::~DeviceTables() {
     if (hipGetDevice(&prev) != hipSuccess) prev = -1;
     if (device >= 0) (void)hipSetDevice(device);
     layouts.clear();
-    void* ptrs[] = {mask, shear, blade, knot_ptr, knot_ent, knot_tap, knots, tw, t_rows, t_cols, t_vox, t_render,
-                    nu_lines, nu_cs, nu_ph, nu_dea, nu_kb, nu_rows};
-    for (void* p : ptrs)
-        if (p) (void)hipFree(p);
+    if (base) (void)hipFree(base);
+    if (nu_base) (void)hipFree(nu_base);
     if (prev >= 0) (void)hipSetDevice(prev);
 }
 
@@ -43,15 +111,57 @@ vp_status hip_status(hipError_t e, const char* what) {
     return fail(VP_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
-template <typename T>
-static hipError_t upload(T** dst, const std::vector<T>& src) {
-    *dst = nullptr;
-    const size_t bytes = std::max<size_t>(sizeof(T), src.size() * sizeof(T));
-    hipError_t e = hipMalloc((void**)dst, bytes);
-    if (e != hipSuccess) return e;
-    if (src.empty()) return hipMemset(*dst, 0, bytes);
-    return hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
-}
+// Tables uploaded together: one allocation, each table on a 256-byte boundary, the small ones by
+// one copy (an allocation and a copy for each of a plan's twenty tables was most of the host time
+// of its first call).
+namespace {
+struct Upload {
+    static constexpr size_t kAlign = 256, kSmall = 65536;
+    struct Piece {
+        const void* src;
+        size_t bytes, room, at;
+        void** dst;
+    };
+    Piece piece[12];
+    int n = 0;
+    template <typename T>
+    Upload& add(T** dst, const std::vector<T>& src) {
+        const size_t bytes = src.size() * sizeof(T);
+        piece[n++] = {src.data(), bytes, (std::max(bytes, sizeof(T)) + kAlign - 1) / kAlign * kAlign, 0, (void**)dst};
+        return *this;
+    }
+    // The allocation (the caller's to free) goes to *base, its tables' addresses to their places.
+    hipError_t go(void** base) {
+        size_t total = 0, small = 0;
+        for (int big = 0; big < 2; ++big) {
+            for (int i = 0; i < n; ++i) {
+                if ((piece[i].bytes > kSmall) != (big == 1)) continue;
+                piece[i].at = total;
+                total += piece[i].room;
+            }
+            if (!big) small = total;
+        }
+        std::unique_ptr<char[]> host(new (std::nothrow) char[small + 1]());
+        if (!host) return hipErrorOutOfMemory;
+        char* d = nullptr;
+        hipError_t e = hipMalloc((void**)&d, total);
+        if (e != hipSuccess) return e;
+        for (int i = 0; i < n; ++i)
+            if (piece[i].bytes && piece[i].bytes <= kSmall) std::memcpy(host.get() + piece[i].at, piece[i].src, piece[i].bytes);
+        if (small) e = hipMemcpy(d, host.get(), small, hipMemcpyHostToDevice);
+        for (int i = 0; i < n; ++i)
+            if (e == hipSuccess && piece[i].bytes > kSmall)
+                e = hipMemcpy(d + piece[i].at, piece[i].src, piece[i].bytes, hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(d);
+            return e;
+        }
+        for (int i = 0; i < n; ++i) *piece[i].dst = d + piece[i].at;
+        *base = d;
+        return hipSuccess;
+    }
+};
+}  // namespace
 
 vp_status plan_tables(const vp_plan* p, DeviceTables** out) {
     int dev = 0;
@@ -66,24 +176,12 @@ vp_status plan_tables(const vp_plan* p, DeviceTables** out) {
     std::unique_ptr<DeviceTables> t(new (std::nothrow) DeviceTables());
     if (!t) return fail(VP_ERR_NOMEM, "plan tables: out of host memory");
     t->device = dev;
-#define UP(field, vec)                                         \
-    do {                                                       \
-        e = upload(&t->field, vec);                            \
-        if (e != hipSuccess) return hip_status(e, "plan tables"); \
-    } while (0)
-    UP(mask, p->mask);
-    UP(shear, p->shear);
-    UP(blade, p->blade);
-    UP(knot_ptr, p->knot_ptr);
-    UP(knot_ent, p->knot_ent);
-    UP(knot_tap, p->knot_tap);
-    UP(knots, p->knots);
-    UP(tw, p->tw);
-    UP(t_rows, p->t_rows);
-    UP(t_cols, p->t_cols);
-    UP(t_vox, p->t_vox);
-    UP(t_render, p->t_render);
-#undef UP
+    Upload up;
+    up.add(&t->mask, p->mask).add(&t->shear, p->shear).add(&t->blade, p->blade);
+    up.add(&t->knot_ptr, p->knot_ptr).add(&t->knot_ent, p->knot_ent).add(&t->knot_tap, p->knot_tap);
+    up.add(&t->knots, p->knots).add(&t->tw, p->tw).add(&t->t_rows, p->t_rows).add(&t->t_cols, p->t_cols);
+    up.add(&t->t_vox, p->t_vox).add(&t->t_render, p->t_render);
+    if ((e = up.go(&t->base)) != hipSuccess) return hip_status(e, "plan tables");
     *out = t.get();
     p->dev.emplace(dev, std::move(t));
     return VP_OK;
@@ -102,10 +200,9 @@ vp_status device_layout(const vp_plan* p, DeviceTables* t, const Layout* L, cons
     if (prev != t->device && (e = hipSetDevice(t->device)) != hipSuccess) return hip_status(e, "hipSetDevice");
     std::unique_ptr<DeviceLayout> d(new (std::nothrow) DeviceLayout());
     if (!d) return fail(VP_ERR_NOMEM, "layout tables: out of host memory");
-    e = upload(&d->groups, L->groups);
-    if (e == hipSuccess) e = upload(&d->t_proj, L->t_proj);
-    if (e == hipSuccess) e = upload(&d->t_gath, L->t_gath);
-    if (e == hipSuccess) e = upload(&d->t_upd, L->t_upd);
+    Upload up;
+    up.add(&d->groups, L->groups).add(&d->t_proj, L->t_proj).add(&d->t_gath, L->t_gath).add(&d->t_upd, L->t_upd);
+    e = up.go(&d->base);
     if (prev != t->device) (void)hipSetDevice(prev);
     if (e != hipSuccess) return hip_status(e, "layout tables");
     *out = d.get();
@@ -291,6 +388,7 @@ struct OpScope {
     const Layout* lay = nullptr;
     const DeviceLayout* dl = nullptr;
     hipStream_t s;
+    Workspace mem;
     float2* work = nullptr;
     explicit OpScope(const vp_plan* plan, void* stream) : p(plan), s((hipStream_t)stream) {}
     vp_status begin(bool need_work) {
@@ -304,13 +402,11 @@ struct OpScope {
         if (st != VP_OK) return st;
         if (need_work) {
             const size_t bytes = (size_t)p->nparts * p->blade_px() * sizeof(float2);
-            hipError_t e = hipMallocAsync((void**)&work, bytes, s);
+            hipError_t e = mem.take(&t->work, bytes, s);
             if (e != hipSuccess) return hip_status(e, "workspace");
+            work = (float2*)mem.ptr;
         }
         return VP_OK;
-    }
-    ~OpScope() {
-        if (work) (void)hipFreeAsync(work, s);
     }
 };
 
@@ -507,13 +603,10 @@ namespace vp {
 vp_status nu_tables(const vp_plan* p, const NuHost* h, DeviceTables* t) {
     std::lock_guard<std::mutex> lk(p->mu);
     if (t->nu_kb) return VP_OK;
-    hipError_t e = upload(&t->nu_lines, h->lines);
-    if (e == hipSuccess) e = upload(&t->nu_cs, h->cs);
-    if (e == hipSuccess) e = upload(&t->nu_ph, h->ph);
-    if (e == hipSuccess) e = upload(&t->nu_dea, h->dea);
-    if (e == hipSuccess) e = upload(&t->nu_kb, h->kb);
-    if (e == hipSuccess) e = upload(&t->nu_rows, h->rows);
-    return hip_status(e, "blade sampling tables");
+    Upload up;
+    up.add(&t->nu_lines, h->lines).add(&t->nu_cs, h->cs).add(&t->nu_ph, h->ph).add(&t->nu_dea, h->dea);
+    up.add(&t->nu_kb, h->kb).add(&t->nu_rows, h->rows);
+    return hip_status(up.go(&t->nu_base), "blade sampling tables");
 }
 
 }  // namespace vp
@@ -534,7 +627,8 @@ struct NuScope {
     unsigned sseed = 0;
     int* stepp = nullptr;
     hipStream_t s;
-    bool persistent = false;  // grids from hipMalloc (a fit), else stream-ordered (an operator call)
+    bool persistent = false;  // grids from hipMalloc (a fit), else a workspace (an operator call)
+    Workspace mem;
     NuArgs d{};
     explicit NuScope(hipStream_t stream, bool keep = false) : s(stream), persistent(keep) {}
     vp_status begin(const vp_plan* p, DeviceTables* t) {
@@ -547,8 +641,9 @@ struct NuScope {
         // the grids, then the premultiplied samples the spread reads
         const size_t ngrid = (size_t)p->B * q->n * q->n, nsamp = (size_t)p->B * h->lmax * p->n;
         const size_t bytes = (ngrid + nsamp) * sizeof(float2);
-        hipError_t e = persistent ? hipMalloc((void**)&grid, bytes) : hipMallocAsync((void**)&grid, bytes, s);
+        hipError_t e = persistent ? hipMalloc((void**)&grid, bytes) : mem.take(&t->work, bytes, s);
         if (e != hipSuccess) return hip_status(e, "oversampled grids");
+        if (!persistent) grid = (float2*)mem.ptr;
         d.n = p->n; d.M = q->n; d.B = p->B; d.lmax = h->lmax; d.nparts = p->nparts; d.kmax = h->kmax;
         d.dw = 1.0f;
         d.lines = t->nu_lines; d.cs = t->nu_cs; d.dea = t->nu_dea; d.kb = t->nu_kb;  d.ph = t->nu_ph;
@@ -589,13 +684,9 @@ struct NuScope {
     }
     enum { ROWS_FWD = 0, COLS_FWD = 1, COLS_INV = 2, ROWS_INV = 3 };
     ~NuScope() {
-        if (!grid) return;
-        if (persistent) {
-            (void)hipStreamSynchronize(s);
-            (void)hipFree(grid);
-        } else {
-            (void)hipFreeAsync(grid, s);
-        }
+        if (!grid || !persistent) return;
+        (void)hipStreamSynchronize(s);
+        (void)hipFree(grid);
     }
 };
 
@@ -954,12 +1045,6 @@ extern "C" vp_status vp_tv_grad(const vp_plan* p, const vp_c64* d_vol, float tv_
     return hip_status(e, "vp_tv_grad");
 }
 
-namespace {
-__global__ void k_set_counter(int* p, int v) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *p = v;
-}
-}  // namespace
-
 extern "C" vp_status vp_step(const vp_plan* p, const vp_options* o, const vp_c64* d_vol, const vp_c64* d_grad,
                              vp_c64* d_m, vp_c64* d_v, int64_t t, vp_c64* d_vol_out, void* stream) {
     clear_error();
@@ -995,21 +1080,13 @@ extern "C" vp_status vp_step(const vp_plan* p, const vp_options* o, const vp_c64
     a.one.m = (float2*)d_m;
     a.one.v = (float2*)d_v;
     a.one.step_limit = 0x7fffffff;
-    int* cnt = nullptr;
-    hipError_t e = hipMallocAsync((void**)&cnt, 256, sc.s);
-    if (e != hipSuccess) return hip_status(e, "vp_step counter");
-    hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(64), 0, sc.s, cnt, s0);
-    e = hipGetLastError();
-    a.one.step = cnt;
+    a.step0 = s0;
     const StageLists L = plan_lists(p, sc.t, lay, dl);
     a.epi = epi_for(o->optimizer, o->tv_weight, o->l1_weight);
     a.stream = stream_for(p->voxels(), o->optimizer);
     a.tasks = L.upd;
     a.ntasks = L.n_upd;
-    if (e == hipSuccess) e = launch_update(a, tl.upd_sc, sc.s);
-    const hipError_t fe = hipFreeAsync(cnt, sc.s);
-    if (e == hipSuccess) e = fe;
-    return hip_status(e, "vp_step");
+    return hip_status(launch_update(a, tl.upd_sc, sc.s), "vp_step");
 }
 
 extern "C" vp_status vp_render(const vp_plan* p, const vp_c64* d_vol, int32_t split_bin, vp_c64* d_proj,

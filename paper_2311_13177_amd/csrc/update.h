@@ -297,11 +297,11 @@ __device__ __forceinline__ UpdateArgs update_args(const KArgs& a, int slice, int
 // slice's hyperparameters (block 0 of the step's last kernel advances the step counter).
 // PRE: the moments come from load_moments (pm, pv) instead of being loaded here.
 template <int SCM, int PPT, int EPI, bool PRE>
-__device__ __forceinline__ void update_and_finish(const KArgs& a, int slice, int* stepp, int st,
+__device__ __forceinline__ void update_and_finish(const KArgs& a, int slice, int st,
                                                   const float2 (&acc)[SCM][PPT], const float2 (&pm)[SCM][PPT],
                                                   const float2 (&pv)[SCM][PPT], int kt, int y0, int x0,
                                                   int lane, int sw, int ns) {
-    const float2* const Vin = stepp ? DF(vol[st & 1]) : DF(vol[0]);
+    const float2* const Vin = DF(vol[st & 1]);
     float2* const Vout = DF(vol[(st + 1) & 1]);
     const UpdateArgs u = update_args(a, slice, st, kt, y0, x0, lane, sw, ns);
     update_column<SCM, PPT, EPI, PRE>(acc, pm, pv, Vin, Vout, DF(m), DF(v), u);

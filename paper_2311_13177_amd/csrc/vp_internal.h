@@ -188,6 +188,7 @@ struct KArgs {
     int snap;
     int advance;
     int nslices;
+    int step0;  // update pass without a step counter: the 0-based step
 };
 
 // The allocation of a fit's step counter holds, kSnapWord ints after the counter, the
