@@ -21,8 +21,43 @@ __device__ __forceinline__ float2 cjmad(float2 a, float2 b, float2 c) {
 // (1 - w) a + w b
 __device__ __forceinline__ float2 clerp(float2 a, float2 b, float w) { return cfma(w, b, cscale(a, 1.0f - w)); }
 
-__device__ __forceinline__ long long gtid() { return (long long)blockIdx.x * blockDim.x + threadIdx.x; }
-__device__ __forceinline__ long long gstride() { return (long long)gridDim.x * blockDim.x; }
+typedef float f32v4 __attribute__((ext_vector_type(4)));
+
+// Indices are split by 32-bit divisions; a fit's element counts fit 31 bits (2 scales x 256 bins x
+// 256 blades x 512 samples x 16 features is the most). The kernels over a decode's times, whose
+// number is the caller's, are compiled for 64 bits too (Ix).
+__device__ __forceinline__ unsigned gtid() { return blockIdx.x * blockDim.x + threadIdx.x; }
+__device__ __forceinline__ unsigned gstride() { return gridDim.x * blockDim.x; }
+
+// Feature-planar arrays (Z, Zt, XA) hold row r's features in pairs (single with F = 1): feature f
+// of sample i at ((r (F / P) + f / P) n + i) P + f % P, P = min(F, 2). A wave of 64 samples then
+// reads 16 contiguous bytes per lane, one access for two features.
+__device__ __forceinline__ int feat_pair(int F) { return F > 1 ? 2 : 1; }
+template <int F>
+__device__ __forceinline__ void load_planar(float2 (&o)[F], const float2* row, int n, int i) {
+    if constexpr (F == 1) {
+        o[0] = row[i];
+    } else {
+#pragma unroll
+        for (int u = 0; u < F / 2; ++u) {
+            const float4 q = *reinterpret_cast<const float4*>(row + 2 * ((size_t)u * n + i));
+            o[2 * u] = make_float2(q.x, q.y);
+            o[2 * u + 1] = make_float2(q.z, q.w);
+        }
+    }
+}
+// One sample's features in a row of [n][F], the same for the whole wave (scalar loads).
+template <int F>
+__device__ __forceinline__ void load_uniform(float2 (&o)[F], const float2* p) {
+    typedef float vec __attribute__((ext_vector_type(2 * (F > 8 ? 8 : F))));
+    constexpr int FV = F > 8 ? 8 : F;
+#pragma unroll
+    for (int u = 0; u < F / FV; ++u) {
+        const vec q = *cst(reinterpret_cast<const vec*>(p + u * FV));
+#pragma unroll
+        for (int f = 0; f < FV; ++f) o[u * FV + f] = make_float2(q[2 * f], q[2 * f + 1]);
+    }
+}
 
 // Grid value of scale c along one spatial axis at sample i: p[stride * node] rows.
 __device__ __forceinline__ float2 read_x(const float2* p, long long stride, const KPDesc& d, int c, int i) {
@@ -35,12 +70,12 @@ __device__ __forceinline__ float2 read_x(const float2* p, long long stride, cons
 
 // Xs, Ys [ns][S][n][F]
 __global__ __launch_bounds__(kThreads) void k_kp_fac_s(const KPDesc d) {
-    const long long total = (long long)d.ns * d.S * d.n * d.F;
-    for (long long e = gtid(); e < total; e += gstride()) {
+    const unsigned total = (unsigned)d.ns * d.S * d.n * d.F;
+    for (unsigned e = gtid(); e < total; e += gstride()) {
         const int f = (int)(e % d.F);
         const int i = (int)((e / d.F) % d.n);
-        const int s = (int)((e / ((long long)d.F * d.n)) % d.S);
-        const int c = (int)(e / ((long long)d.F * d.n * d.S));
+        const int s = (int)((e / ((unsigned)d.F * d.n)) % d.S);
+        const int c = (int)(e / ((unsigned)d.F * d.n * d.S));
         const int R = d.R[c];
         const float2* xs = d.params + d.off[c][KP_XS] + (long long)s * R * d.F + f;
         const float2* ys = d.params + d.off[c][KP_YS] + (long long)s * R * d.F + f;
@@ -50,15 +85,16 @@ __global__ __launch_bounds__(kThreads) void k_kp_fac_s(const KPDesc d) {
 }
 
 // qx, qy [ns][B][n][F] and qs [ns][B][S][F]: time grids at each time
+template <typename Ix>
 __global__ __launch_bounds__(kThreads) void k_kp_fac_t(const KPDesc d) {
-    const long long nq = (long long)d.ns * d.B * d.n * d.F;
-    const long long total = nq + (long long)d.ns * d.B * d.S * d.F;
-    for (long long e = gtid(); e < total; e += gstride()) {
+    const Ix nq = (Ix)d.ns * d.B * d.n * d.F;
+    const Ix total = nq + (Ix)d.ns * d.B * d.S * d.F;
+    for (Ix e = gtid(); e < total; e += gstride()) {
         if (e < nq) {
             const int f = (int)(e % d.F);
             const int i = (int)((e / d.F) % d.n);
-            const int b = (int)((e / ((long long)d.F * d.n)) % d.B);
-            const int c = (int)(e / ((long long)d.F * d.n * d.B));
+            const int b = (int)((e / ((Ix)d.F * d.n)) % d.B);
+            const int c = (int)(e / ((Ix)d.F * d.n * d.B));
             const int R = d.R[c];
             const int k0 = d.tk[b], k1 = min(k0 + 1, d.Rt - 1);
             const float a = d.ta[b];
@@ -68,11 +104,11 @@ __global__ __launch_bounds__(kThreads) void k_kp_fac_t(const KPDesc d) {
             d.qx[e] = clerp(read_x(xt + k0 * row, d.F, d, c, i), read_x(xt + k1 * row, d.F, d, c, i), a);
             d.qy[e] = clerp(read_x(yt + k0 * row, d.F, d, c, i), read_x(yt + k1 * row, d.F, d, c, i), a);
         } else {
-            const long long r = e - nq;
+            const Ix r = e - nq;
             const int f = (int)(r % d.F);
             const int s = (int)((r / d.F) % d.S);
-            const int b = (int)((r / ((long long)d.F * d.S)) % d.B);
-            const int c = (int)(r / ((long long)d.F * d.S * d.B));
+            const int b = (int)((r / ((Ix)d.F * d.S)) % d.B);
+            const int c = (int)(r / ((Ix)d.F * d.S * d.B));
             const int k0 = d.tk[b], k1 = min(k0 + 1, d.Rt - 1);
             const float2* st = d.params + d.off[c][KP_ST] + (long long)s * d.F + f;
             const long long row = (long long)d.S * d.F;
@@ -81,122 +117,109 @@ __global__ __launch_bounds__(kThreads) void k_kp_fac_t(const KPDesc d) {
     }
 }
 
-// Z [ns][n][n][F]: the xy grid at (y, x), along x first
+// Z: the xy grid at (y, x), along x first, feature-planar with rows y; Zt the same values with
+// rows x (each written in its own order)
 __global__ __launch_bounds__(kThreads) void k_kp_fac_z(const KPDesc d) {
-    const long long total = (long long)d.ns * d.n * d.n * d.F;
-    for (long long e = gtid(); e < total; e += gstride()) {
-        const int f = (int)(e % d.F);
-        const int x = (int)((e / d.F) % d.n);
-        const int y = (int)((e / ((long long)d.F * d.n)) % d.n);
-        const int c = (int)(e / ((long long)d.F * d.n * d.n));
+    const unsigned per = (unsigned)d.ns * d.n * d.n * d.F, P = feat_pair(d.F);
+    const unsigned total = d.Zt ? 2 * per : per;
+    for (unsigned e = gtid(); e < total; e += gstride()) {
+        const bool tr = e >= per;
+        const unsigned q = tr ? e - per : e;
+        const int i = (int)((q / P) % d.n);
+        const unsigned ru = q / (P * d.n);  // row and feature pair
+        const int f = (int)((ru % (d.F / P)) * P + q % P);
+        const int r = (int)((ru / (d.F / P)) % d.n);
+        const int c = (int)(ru / (d.F / P) / d.n);
+        const int x = tr ? r : i, y = tr ? i : r;
         const int R = d.R[c];
         const float2* xy = d.params + d.off[c][KP_XY] + f;
         const int j0 = d.nd0[c * d.n + y], j1 = min(j0 + 1, R - 1);
         const float2 r0 = read_x(xy + (long long)j0 * R * d.F, d.F, d, c, x);
         const float2 r1 = read_x(xy + (long long)j1 * R * d.F, d.F, d, c, x);
-        d.Z[e] = clerp(r0, r1, d.ndw[c * d.n + y]);
+        (tr ? d.Zt : d.Z)[q] = clerp(r0, r1, d.ndw[c * d.n + y]);
     }
 }
 
-// XA = a Xs qx qs and Yf = Ys qy, [ns][B][S][n][F]
+// XA = a Xs qx qs, [ns][B][S] rows feature-planar, the same as [ns][B][S][n][F] (XAt), and
+// Yf = Ys qy, [ns][B][S][n][F]
+template <typename Ix>
 __global__ __launch_bounds__(kThreads) void k_kp_prod(const KPDesc d) {
-    const long long total = (long long)d.ns * d.B * d.S * d.n * d.F;
-    for (long long e = gtid(); e < total; e += gstride()) {
-        const int f = (int)(e % d.F);
-        const int i = (int)((e / d.F) % d.n);
-        const int s = (int)((e / ((long long)d.F * d.n)) % d.S);
-        const int b = (int)((e / ((long long)d.F * d.n * d.S)) % d.B);
-        const int c = (int)(e / ((long long)d.F * d.n * d.S * d.B));
-        const long long xs = (((long long)c * d.S + s) * d.n + i) * d.F + f;
-        const long long qi = (((long long)c * d.B + b) * d.n + i) * d.F + f;
-        const long long qsi = (((long long)c * d.B + b) * d.S + s) * d.F + f;
-        const float2 a = d.params[d.a_off + f];
-        d.XA[e] = cmul(cmul(cmul(a, d.Xs[xs]), d.qx[qi]), d.qs[qsi]);
-        d.Yf[e] = cmul(d.Ys[xs], d.qy[qi]);
+    const Ix total = (Ix)d.ns * d.B * d.S * d.n * d.F;
+    const unsigned P = feat_pair(d.F), FN = (Ix)d.F * d.n;
+    for (Ix e = gtid(); e < total; e += gstride()) {
+        const Ix row = e / FN;
+        const unsigned in = (unsigned)(e - row * FN);  // row (c, b, s)
+        const Ix cb = row / d.S, s = row - cb * d.S;
+        const Ix cs = cb / d.B * d.S + s;
+        auto xa = [&](unsigned i, unsigned f) {
+            return cmul(cmul(cmul(d.params[d.a_off + f], d.Xs[cs * FN + i * d.F + f]), d.qx[cb * FN + i * d.F + f]),
+                        d.qs[row * d.F + f]);
+        };
+        const unsigned u = in / (P * d.n);
+        d.XA[e] = xa(in / P - u * d.n, u * P + in % P);
+        if (d.XAt) d.XAt[e] = xa(in / d.F, in % d.F);
+        d.Yf[e] = cmul(d.Ys[cs * FN + in], d.qy[cb * FN + in]);
     }
 }
 
 // ------------------------------------------------------------------ decode
 
 // vol[b][s][y][x] = sum_c sum_f Z[c][y][x][f] XA[c][b][s][x][f] Yf[c][b][s][y][f]
-constexpr int kDecBins = 4;
-
-// Values that are the same for a whole wave are loaded spread over its lanes, one vector
-// load for up to 64 of them, and read back with lane_f2.
-constexpr int kDecRows = 4;
-
+//
 // A wave task is (blade, kDecBins bins, kDecRows rows, 64 columns): its XA values (per
 // column) are loaded once for all kDecRows rows, its Yf values (per row, the same in
-// every lane) once for the wave spread over the lanes, and Z (per pixel) once per row for
-// all kDecBins bins. The sums run in the same order as a per-voxel loop (scales, then
-// features), so every shape of this task gives the same bits.
+// every lane) by scalar loads, and Z (per pixel) once per row for all kDecBins bins. A block's
+// four waves take two neighbouring row groups by two bin groups, so that each value read is
+// used by two waves of the CU, and the blocks of an XCD share rows (their Z stays in its L2).
+// The sums run in the same order as a per-voxel loop (scales, then features), so every shape
+// of this task gives the same bits. Its FP32 operations are the bound (8 per voxel, feature
+// and scale: 123 us at the full clock for 32 blades x 32 bins x 192^2, 8 features, 2 scales;
+// 195 us taken in a fit, 232 with four bins a wave, where half the waves fit).
+constexpr int kDecBins = 2;
+constexpr int kDecRows = 4;
+
 template <int F>
 __global__ __launch_bounds__(kThreads) void k_kp_decode(const KPDesc d) {
-    constexpr int NY = kDecRows * kKpMaxScales * kDecBins * F;  // Yf entries of one wave task
-    constexpr int NL = (NY + 63) / 64;
     const int n = d.n, S = d.S;
     const long long nn = (long long)n * n;
-    const int sq = (S + kDecBins - 1) / kDecBins;
-    const int nseg = (n + 63) / 64, nrg = (n + kDecRows - 1) / kDecRows;
+    const int sqp = (S + 2 * kDecBins - 1) / (2 * kDecBins);
+    const int nseg = (n + 63) / 64, nrp = (n + 2 * kDecRows - 1) / (2 * kDecRows);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long W = (long long)d.B * sq * nrg * nseg;
-    for (long long w = (long long)blockIdx.x * (kThreads / 64) + wave; w < W; w += (long long)gridDim.x * (kThreads / 64)) {
-        const int seg = (int)(w % nseg);
-        const int rg = (int)((w / nseg) % nrg);
-        const int q = (int)((w / ((long long)nseg * nrg)) % sq);
-        const int b = (int)(w / ((long long)nseg * nrg * sq));
-        const int s0 = q * kDecBins, ns = min(kDecBins, S - s0);
-        const int y0 = rg * kDecRows;
-        // Yf of the task, one entry per lane: ((r kKpMaxScales + c) kDecBins + k) F + f
-        float2 yl[NL];
-#pragma unroll
-        for (int t = 0; t < NL; ++t) {
-            const int ei = t * 64 + lane;
-            const int f = ei % F, k = (ei / F) % kDecBins, c = (ei / (F * kDecBins)) % kKpMaxScales;
-            const int r = ei / (F * kDecBins * kKpMaxScales);
-            yl[t] = make_float2(0.f, 0.f);
-            if (ei < NY && c < d.ns && k < ns && y0 + r < n)
-                yl[t] = d.Yf[((((long long)c * d.B + b) * S + s0 + k) * n + y0 + r) * F + f];
-        }
+    const unsigned W = (unsigned)d.B * sqp * nrp * nseg;
+    for (unsigned w = xcd_item(blockIdx.x, gridDim.x); w < W; w += gridDim.x) {
+        const int qp = w % sqp, b = (w / sqp) % d.B, sg = w / ((unsigned)sqp * d.B);
+        const int seg = sg % nseg, rp = sg / nseg;
+        const int s0 = (qp * 2 + (wave >> 1)) * kDecBins, ns = min(kDecBins, S - s0);
+        const int y0 = (rp * 2 + (wave & 1)) * kDecRows;
+        if (ns <= 0 || y0 >= n) continue;
         const int x = seg * 64 + lane;
-        const bool live = x < n;
-        const int xs = live ? x : 0;
+        const int xs = min(x, n - 1);
         float2 v[kDecRows][kDecBins];
 #pragma unroll
         for (int r = 0; r < kDecRows; ++r)
 #pragma unroll
             for (int k = 0; k < kDecBins; ++k) v[r][k] = make_float2(0.f, 0.f);
+        for (int c = 0; c < d.ns; ++c) {
+            const long long cb = ((long long)c * d.B + b) * S + s0;
+            float2 xa[kDecBins][F];
 #pragma unroll
-        for (int c = 0; c < kKpMaxScales; ++c) {
-            if (c < d.ns) {
-                float2 xa[kDecBins][F];
+            for (int k = 0; k < kDecBins; ++k) load_planar<F>(xa[k], d.XA + (cb + min(k, ns - 1)) * n * F, n, xs);
+#pragma unroll
+            for (int r = 0; r < kDecRows; ++r) {
+                const int y = min(y0 + r, n - 1);
+                float2 z[F];
+                load_planar<F>(z, d.Z + ((long long)c * n + y) * n * F, n, xs);
 #pragma unroll
                 for (int k = 0; k < kDecBins; ++k) {
-                    const long long cb = ((long long)c * d.B + b) * S + s0 + min(k, ns - 1);
-                    const float2* xp = d.XA + (cb * n + xs) * F;
+                    float2 yf[F];
+                    load_uniform<F>(yf, d.Yf + ((cb + min(k, ns - 1)) * n + y) * F);
 #pragma unroll
-                    for (int f = 0; f < F; ++f) xa[k][f] = xp[f];
-                }
-#pragma unroll
-                for (int r = 0; r < kDecRows; ++r) {
-                    const int y = min(y0 + r, n - 1);
-                    float2 z[F];
-                    const float2* zp = d.Z + ((long long)c * nn + (long long)y * n + xs) * F;
-#pragma unroll
-                    for (int f = 0; f < F; ++f) z[f] = zp[f];
-#pragma unroll
-                    for (int k = 0; k < kDecBins; ++k) {
-#pragma unroll
-                        for (int f = 0; f < F; ++f) {
-                            const int ei = ((r * kKpMaxScales + c) * kDecBins + k) * F + f;
-                            v[r][k] = cmad(cmul(z[f], xa[k][f]), lane_f2(yl[ei / 64], ei % 64), v[r][k]);
-                        }
-                    }
+                    for (int f = 0; f < F; ++f) v[r][k] = cmad(cmul(z[f], xa[k][f]), yf[f], v[r][k]);
                 }
             }
         }
-        if (live) {
+        if (x < n) {
 #pragma unroll
             for (int r = 0; r < kDecRows; ++r)
 #pragma unroll
@@ -211,29 +234,28 @@ __global__ __launch_bounds__(kThreads) void k_kp_decode(const KPDesc d) {
 // gZ[c][y][x][f] = sum_b sum_s conj(XA Yf) G[b][s][y][x], in two passes: partial sums over
 // consecutive (b, s) chunks for every pixel and both scales (G read once), then the
 // chunks summed in order. A wave task of the first pass is (chunk, kGzRows rows, 64
-// columns): each XA value (per column) serves all kGzRows rows, and the Yf values (per
-// row, the same in every lane) of 64 / (kGzRows kKpMaxScales F) consecutive (b, s) are
-// loaded at once spread over the lanes. Each sum runs over (b, s) in order.
+// columns): each XA value (per column) serves all kGzRows rows, the Yf values (per row, the
+// same in every lane) are scalar loads, and a block's four waves take neighbouring rows of
+// one chunk, so that XA comes from the CU's cache for three of them. Each sum runs over
+// (b, s) in order. Bound by its FP32 operations (123 us at the sizes above; 200 us, 296 with
+// XA as [n][F], four waves a block without a value in common and a last round of few blocks).
 constexpr int kGzRows = 2;
 
 template <int F>
 __global__ __launch_bounds__(kThreads) void k_kp_grad_z(const KPDesc d) {
-    constexpr int NYB = kGzRows * kKpMaxScales * F;  // Yf entries per (b, s)
-    constexpr int BPL = NYB >= 64 ? 1 : 64 / NYB;     // (b, s) per lane-spread load
     const int n = d.n;
     const long long nn = (long long)n * n;
     const int nbs = d.B * d.S, cs = (nbs + d.zchunks - 1) / d.zchunks;
-    const int nseg = (n + 63) / 64, nrg = (n + kGzRows - 1) / kGzRows;
+    const int nseg = (n + 63) / 64, nrb = (n + 4 * kGzRows - 1) / (4 * kGzRows);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long W = (long long)d.zchunks * nrg * nseg;
-    for (long long w = (long long)blockIdx.x * (kThreads / 64) + wave; w < W; w += (long long)gridDim.x * (kThreads / 64)) {
-        const int seg = (int)(w % nseg);
-        const int y0 = (int)((w / nseg) % nrg) * kGzRows;
-        const int ch = (int)(w / ((long long)nseg * nrg));
+    const int W = d.zchunks * nrb * nseg;
+    for (int w = xcd_item(blockIdx.x, gridDim.x); w < W; w += gridDim.x) {
+        const int y0 = ((w % nrb) * 4 + wave) * kGzRows;
+        const int seg = (w / nrb) % nseg, ch = w / (nrb * nseg);
+        if (y0 >= n) continue;
         const int x = seg * 64 + lane;
-        const bool live = x < n;
-        const int xs = live ? x : 0;
+        const int xs = min(x, n - 1);
         float2 acc[kGzRows][kKpMaxScales][F];
 #pragma unroll
         for (int r = 0; r < kGzRows; ++r)
@@ -242,45 +264,27 @@ __global__ __launch_bounds__(kThreads) void k_kp_grad_z(const KPDesc d) {
 #pragma unroll
                 for (int f = 0; f < F; ++f) acc[r][c][f] = make_float2(0.f, 0.f);
         const int bs1 = min(nbs, (ch + 1) * cs);
-        for (int bs = ch * cs; bs < bs1; bs += BPL) {
-            float2 yl;
-            {
-                const int bq = bs + lane / NYB, ei = lane % NYB;
-                const int r = ei / (kKpMaxScales * F), c = (ei / F) % kKpMaxScales, f = ei % F;
-                yl = make_float2(0.f, 0.f);
-                if (lane < BPL * NYB && bq < bs1 && c < d.ns && y0 + r < n)
-                    yl = d.Yf[(((long long)c * nbs + bq) * n + y0 + r) * F + f];
-            }
+        for (int bs = ch * cs; bs < bs1; ++bs) {
+            float2 g[kGzRows];
 #pragma unroll
-            for (int u = 0; u < BPL; ++u) {
-                const int bu = bs + u;
-                if (bu < bs1) {
-                    float2 xa[kKpMaxScales][F];
+            for (int r = 0; r < kGzRows; ++r) g[r] = d.G[(long long)bs * nn + (long long)min(y0 + r, n - 1) * n + xs];
 #pragma unroll
-                    for (int c = 0; c < kKpMaxScales; ++c) {
-                        const float2* xp = d.XA + (((long long)min(c, d.ns - 1) * nbs + bu) * n + xs) * F;
-#pragma unroll
-                        for (int f = 0; f < F; ++f) xa[c][f] = xp[f];
-                    }
+            for (int c = 0; c < kKpMaxScales; ++c) {
+                if (c < d.ns) {
+                    const long long cb = (long long)c * nbs + bs;
+                    float2 xa[F];
+                    load_planar<F>(xa, d.XA + cb * n * F, n, xs);
 #pragma unroll
                     for (int r = 0; r < kGzRows; ++r) {
-                        if (y0 + r < n) {
-                            const float2 g = d.G[(long long)bu * nn + (long long)(y0 + r) * n + xs];
+                        float2 yf[F];
+                        load_uniform<F>(yf, d.Yf + (cb * n + min(y0 + r, n - 1)) * F);
 #pragma unroll
-                            for (int c = 0; c < kKpMaxScales; ++c) {
-                                if (c < d.ns) {
-#pragma unroll
-                                    for (int f = 0; f < F; ++f)
-                                        acc[r][c][f] = cjmad(cmul(xa[c][f], lane_f2(yl, u * NYB + (r * kKpMaxScales + c) * F + f)),
-                                                             g, acc[r][c][f]);
-                                }
-                            }
-                        }
+                        for (int f = 0; f < F; ++f) acc[r][c][f] = cjmad(cmul(xa[f], yf[f]), g[r], acc[r][c][f]);
                     }
                 }
             }
         }
-        if (live) {
+        if (x < n) {
 #pragma unroll
             for (int r = 0; r < kGzRows; ++r) {
 #pragma unroll
@@ -297,171 +301,198 @@ __global__ __launch_bounds__(kThreads) void k_kp_grad_z(const KPDesc d) {
 }
 
 __global__ __launch_bounds__(kThreads) void k_kp_grad_z_sum(const KPDesc d) {
-    const long long per = (long long)d.ns * d.n * d.n * d.F;
-    for (long long e = gtid(); e < per; e += gstride()) {
+    const unsigned per = (unsigned)d.ns * d.n * d.n * d.F;
+    for (unsigned e = gtid(); e < per; e += gstride()) {
         float2 acc = make_float2(0.f, 0.f);
-        for (int ch = 0; ch < d.zchunks; ++ch) acc = cadd(acc, d.zpart[(long long)ch * per + e]);
+        for (int ch = 0; ch < d.zchunks; ++ch) acc = cadd(acc, d.zpart[(size_t)ch * per + e]);
         d.gZ[e] = acc;
     }
 }
 
-// gXA[c][b][s][x][f] = sum_y conj(Z Yf) G[b][s][y][x]. A wave task is (kGxBs consecutive
-// (b, s), 64 columns, one of kGxYs row ranges): each Z value (per pixel) serves all kGxBs
-// (b, s), and the Yf values (per row, the same in every lane) are loaded 64 / F rows at a
-// time spread over the lanes. The row split keeps the waves of one (b, s) per task while
-// Z is shared; each range's sum runs over y in order into its own part of gXA, and
-// k_kp_gx_sum adds the parts in order.
-constexpr int kGxBs = 2;
-constexpr int kGxYs = 2;  // row ranges
+// gXA[c][b][s][x][f] = sum_y conj(Z Yf) G[b][s][y][x] and gY[c][b][s][y][f] =
+// sum_x conj(Z XA) G[b][s][y][x]: the same sum with the axes exchanged. A wave task is
+// (BS consecutive (b, s), 64 lanes along one axis, one of PARTS parts of the other axis): each Z
+// (Zt) value serves all BS (b, s) and both scales' sums read G once; the other factor is the
+// same in every lane (scalar loads). A block is one task: its PARTS waves' sums, each in order, are
+// added through LDS. Bound by its FP32 operations (123 us at the sizes above; gXA 205 us, 296 with
+// G read once per scale, the halves summed by a kernel of their own and Z as [n][F]).
+//
+// Two (b, s) a wave by eight parts (four for gY) halve the loads of Z; one by eight has twice the
+// waves. The second is taken below kGxWaves tasks of one (b, s) (two by eight parts against
+// one by eight, gXA with 8 features: 1024 tasks of 256^2 96 and 144 us, 512 of 128^2 21 and 19 us, 256 of
+// 256^2 63 and 53 us) and with 16 features, whose sums of two leave room for two waves per SIMD (3072 of
+// 192^2: 588 and 508 us).
+constexpr int kGxWaves = 1024;
+constexpr int kGxParts = 8, kGyParts = 4, kWideParts = 8;
+inline bool kp_one_bs(const KPDesc& d) {
+    return d.F > 8 || (long long)d.B * d.S * ((d.n + 63) / 64) < kGxWaves;
+}
 
-template <int F>
-__global__ __launch_bounds__(kThreads) void k_kp_grad_x(const KPDesc d) {
-    constexpr int YB = 64 / F;  // rows per lane-spread Yf load
-    const int n = d.n;
-    const long long nn = (long long)n * n;
-    const int nbs = d.B * d.S;
-    const int nseg = (n + 63) / 64, ngr = (nbs + kGxBs - 1) / kGxBs;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long W = (long long)ngr * nseg * kGxYs;
-    const int rq = (n + kGxYs - 1) / kGxYs;
-    for (long long w = (long long)blockIdx.x * (kThreads / 64) + wave; w < W; w += (long long)gridDim.x * (kThreads / 64)) {
-        const int seg = (int)(w % nseg);
-        const int half = (int)((w / nseg) % kGxYs);
-        const int bs0 = (int)(w / ((long long)nseg * kGxYs)) * kGxBs;
-        const int ya = min(n, half * rq), yb = min(n, ya + rq);
-        const int x = seg * 64 + lane;
-        const bool live = x < n;
-        const int xs = live ? x : 0;
-        for (int c = 0; c < d.ns; ++c) {
-            float2 acc[kGxBs][F];
+// The waves of parts 1.. leave their sums in LDS, one scale at a time, and the first part's
+// wave adds them to its own in order and stores (lane `at` of row c nbs + bs of [n][F]).
+template <int F, int BS, int PARTS>
+__device__ __forceinline__ void add_parts(float2* red, const float2 (&acc)[BS][kKpMaxScales][F], int part, int lane,
+                                          float2* out, int ns, int nbs, int bs0, int n, int at) {
+    constexpr int kOne = BS * F * 64;
+    float2* const mine = red + lane;
 #pragma unroll
-            for (int j = 0; j < kGxBs; ++j)
+    for (int c = 0; c < kKpMaxScales; ++c) {
+        if (c < ns) {
+            __syncthreads();
+            if (part > 0) {
 #pragma unroll
-                for (int f = 0; f < F; ++f) acc[j][f] = make_float2(0.f, 0.f);
-            for (int y0 = ya; y0 < yb; y0 += YB) {
-                float2 yl[kGxBs];
-                const int yy = y0 + lane / F;
+                for (int j = 0; j < BS; ++j)
 #pragma unroll
-                for (int j = 0; j < kGxBs; ++j) {
-                    const int bs = bs0 + j;
-                    yl[j] = make_float2(0.f, 0.f);
-                    if (bs < nbs && yy < yb) yl[j] = d.Yf[(((long long)c * nbs + bs) * n + yy) * F + lane % F];
-                }
-#pragma unroll
-                for (int t = 0; t < YB; ++t) {
-                    const int y = y0 + t;
-                    if (y < yb) {
-                        float2 z[F];
-                        const float2* zp = d.Z + (((long long)c * n + y) * n + xs) * F;
-#pragma unroll
-                        for (int f = 0; f < F; ++f) z[f] = zp[f];
-#pragma unroll
-                        for (int j = 0; j < kGxBs; ++j) {
-                            if (bs0 + j < nbs) {
-                                const float2 g = d.G[(long long)(bs0 + j) * nn + (long long)y * n + xs];
-#pragma unroll
-                                for (int f = 0; f < F; ++f)
-                                    acc[j][f] = cjmad(cmul(z[f], lane_f2(yl[j], t * F + f)), g, acc[j][f]);
-                            }
-                        }
-                    }
-                }
+                    for (int f = 0; f < F; ++f) mine[(part - 1) * kOne + (j * F + f) * 64] = acc[j][c][f];
             }
-            if (live) {
+            __syncthreads();
+            if (part == 0 && at < n) {
 #pragma unroll
-                for (int j = 0; j < kGxBs; ++j) {
+                for (int j = 0; j < BS; ++j) {
                     if (bs0 + j < nbs) {
-                        float2* out = d.gXA + (long long)half * d.ns * nbs * n * F + (((long long)c * nbs + bs0 + j) * n + x) * F;
-#pragma unroll
-                        for (int f = 0; f < F; ++f) out[f] = acc[j][f];
-                    }
-                }
-            }
-        }
-    }
-}
-
-// gXA (part 0) = the sum of the kGxYs row-range parts, in order
-__global__ __launch_bounds__(kThreads) void k_kp_gx_sum(const KPDesc d) {
-    const long long per = (long long)d.ns * d.B * d.S * d.n * d.F;
-    for (long long e = gtid(); e < per; e += gstride()) {
-        float2 v = d.gXA[e];
-        for (int h = 1; h < kGxYs; ++h) v = cadd(v, d.gXA[h * per + e]);
-        d.gXA[e] = v;
-    }
-}
-
-// gY[c][b][s][y][f] = sum_x conj(Z XA) G[b][s][y][x]: one wave per block of 32 / F rows,
-// RB consecutive (b, s) by RY consecutive y (each Z value serves the RB (b, s), each XA
-// value the RY rows), lanes over x; the wave's 64 partial sums per lane (rows x features x
-// re/im) are reduced across lanes by recursive halving, each step sending the half a lane
-// gives up to its partner, so that lane L ends with the total of value L (a fixed order).
-template <int F>
-__global__ __launch_bounds__(kThreads) void k_kp_grad_y(const KPDesc d) {
-    constexpr int RW = 32 / F;  // rows per wave: 2 F RW = 64 values
-    constexpr int RY = RW >= 16 ? 4 : (RW >= 4 ? 2 : 1);
-    constexpr int RB = RW / RY;
-    const int n = d.n;
-    const int lane = threadIdx.x & 63;
-    const int nbs = d.B * d.S;
-    const long long nyb = (n + RY - 1) / RY, nbb = (nbs + RB - 1) / RB;
-    const long long groups = nbb * nyb;
-    for (long long gi = (long long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); gi < groups;
-         gi += (long long)gridDim.x * (kThreads / 64)) {
-        const int y0 = (int)(gi % nyb) * RY;
-        const int bs0 = (int)(gi / nyb) * RB;
-        for (int c = 0; c < d.ns; ++c) {
-            float v[64];
-#pragma unroll
-            for (int i = 0; i < 64; ++i) v[i] = 0.f;
-            for (int x = lane; x < n; x += 64) {
-                float2 zr[RY][F], xr[RB][F];
-#pragma unroll
-                for (int q = 0; q < RY; ++q) {
-                    const float2* z = d.Z + (((long long)c * n + min(y0 + q, n - 1)) * n + x) * F;
-#pragma unroll
-                    for (int f = 0; f < F; ++f) zr[q][f] = z[f];
-                }
-#pragma unroll
-                for (int q = 0; q < RB; ++q) {
-                    const float2* xa = d.XA + (((long long)c * nbs + min(bs0 + q, nbs - 1)) * n + x) * F;
-#pragma unroll
-                    for (int f = 0; f < F; ++f) xr[q][f] = xa[f];
-                }
-#pragma unroll
-                for (int r = 0; r < RW; ++r) {
-                    const int rb = r / RY, ry = r % RY;
-                    if (bs0 + rb < nbs && y0 + ry < n) {
-                        const float2 g = d.G[((long long)(bs0 + rb) * n + y0 + ry) * n + x];
+                        float2* o = out + (((long long)c * nbs + bs0 + j) * n + at) * F;
 #pragma unroll
                         for (int f = 0; f < F; ++f) {
-                            const float2 t = cjmad(cmul(zr[ry][f], xr[rb][f]), g,
-                                                   make_float2(v[(r * F + f) * 2], v[(r * F + f) * 2 + 1]));
-                            v[(r * F + f) * 2] = t.x;
-                            v[(r * F + f) * 2 + 1] = t.y;
+                            float2 v = acc[j][c][f];
+#pragma unroll
+                            for (int q = 0; q < PARTS - 1; ++q) v = cadd(v, mine[q * kOne + (j * F + f) * 64]);
+                            o[f] = v;
                         }
                     }
                 }
             }
+        }
+    }
+}
+
+template <int F, int BS, int PARTS>
+__global__ __launch_bounds__(64 * PARTS) void k_kp_grad_x(const KPDesc d) {
+    __shared__ float2 red[(PARTS - 1) * BS * F * 64];
+    const int n = d.n;
+    const long long nn = (long long)n * n;
+    const int nbs = d.B * d.S, ntp = (nbs + BS - 1) / BS;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int W = ntp * ((n + 63) / 64), rq = (n + PARTS - 1) / PARTS;
+    for (int w = xcd_item(blockIdx.x, gridDim.x); w < W; w += gridDim.x) {
+        const int bs0 = (w % ntp) * BS;
+        const int x = (w / ntp) * 64 + lane, xs = min(x, n - 1);
+        const int ya = wave * rq, yb = bs0 < nbs ? min(n, ya + rq) : 0;
+        float2 acc[BS][kKpMaxScales][F];
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const bool up = (lane & o) != 0;
+        for (int j = 0; j < BS; ++j)
 #pragma unroll
-                for (int i = 0; i < o; ++i) {
-                    const float send = up ? v[i] : v[i + o];
-                    const float keep = up ? v[i + o] : v[i];
-                    v[i] = keep + __shfl_xor(send, o);
+            for (int c = 0; c < kKpMaxScales; ++c)
+#pragma unroll
+                for (int f = 0; f < F; ++f) acc[j][c][f] = make_float2(0.f, 0.f);
+        for (int y = ya; y < yb; ++y) {
+            float2 g[BS];
+#pragma unroll
+            for (int j = 0; j < BS; ++j) g[j] = d.G[(long long)min(bs0 + j, nbs - 1) * nn + (long long)y * n + xs];
+#pragma unroll
+            for (int c = 0; c < kKpMaxScales; ++c) {
+                if (c < d.ns) {
+                    float2 z[F];
+                    load_planar<F>(z, d.Z + ((long long)c * n + y) * n * F, n, xs);
+#pragma unroll
+                    for (int j = 0; j < BS; ++j) {
+                        float2 yf[F];
+                        load_uniform<F>(yf, d.Yf + (((long long)c * nbs + min(bs0 + j, nbs - 1)) * n + y) * F);
+#pragma unroll
+                        for (int f = 0; f < F; ++f) acc[j][c][f] = cjmad(cmul(z[f], yf[f]), g[j], acc[j][c][f]);
+                    }
                 }
             }
-            // lane L holds value L: row L / (2F), feature (L / 2) % F, component L % 2
-            const int r = lane / (2 * F), rb = r / RY, ry = r % RY;
-            if (bs0 + rb < nbs && y0 + ry < n) {
-                const long long cb = (long long)c * nbs + bs0 + rb;
-                float* out = reinterpret_cast<float*>(d.gY + (cb * n + y0 + ry) * F);
-                out[lane % (2 * F)] = v[0];
+        }
+        add_parts<F, BS, PARTS>(red, acc, wave, lane, d.gXA, d.ns, nbs, bs0, n, x);
+    }
+}
+
+// The lanes run over y here, so a wave turns its part of G (64 rows by kGyCols columns of each of
+// its (b, s)) through its own LDS: a lane loads 16 bytes of a row, four lanes a row's 64 bytes,
+// and reads back its own row; the 16-byte units of row r are permuted by (r / 4) % 4, which
+// keeps both sides free of bank conflicts. (gY 200 us at the sizes above; 460 us with the lanes
+// over x, two rows of Z and of XA loaded for four sums and 63 exchanges between lanes at the end.)
+// The parts take groups of kGyCols columns in turn: they use the lines of G that one of them has
+// brought in.
+constexpr int kGyCols = 8;
+
+// PAIR: n is even and G on a 16-byte boundary, so that a lane's two columns are one access (a branch
+// at run time was compiled into four loads for both cases: 277 us instead of 200).
+template <int F, int BS, int PARTS, bool PAIR>
+__global__ __launch_bounds__(64 * PARTS) void k_kp_grad_y(const KPDesc d) {
+    constexpr int kTile = 64 * kGyCols;  // values of one (b, s)
+    constexpr int kRed = (PARTS - 1) * BS * F * 64, kTiles = PARTS * BS * kTile;
+    __shared__ __attribute__((aligned(16))) float2 red[kRed > kTiles ? kRed : kTiles];
+    const int n = d.n;
+    const long long nn = (long long)n * n;
+    const int nbs = d.B * d.S, ntp = (nbs + BS - 1) / BS;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    f32v4* const tile = reinterpret_cast<f32v4*>(red + wave * BS * kTile);
+    const int W = ntp * ((n + 63) / 64);
+    for (int w = xcd_item(blockIdx.x, gridDim.x); w < W; w += gridDim.x) {
+        const int bs0 = (w % ntp) * BS;
+        const int y0 = (w / ntp) * 64;
+        const int y = y0 + lane, ys = min(y, n - 1);
+        const int xb = bs0 < nbs ? n : 0;
+        float2 acc[BS][kKpMaxScales][F];
+#pragma unroll
+        for (int j = 0; j < BS; ++j)
+#pragma unroll
+            for (int c = 0; c < kKpMaxScales; ++c)
+#pragma unroll
+                for (int f = 0; f < F; ++f) acc[j][c][f] = make_float2(0.f, 0.f);
+        __syncthreads();  // the sums of the item before are read from the tiles' memory
+        for (int x0 = wave * kGyCols; x0 < xb; x0 += PARTS * kGyCols) {
+            f32v4 t[BS][4];
+#pragma unroll
+            for (int j = 0; j < BS; ++j) {
+                const float2* G = d.G + (long long)min(bs0 + j, nbs - 1) * nn;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float2* row = G + (long long)min(y0 + i * 16 + lane / 4, n - 1) * n;
+                    const int xc = x0 + 2 * (lane % 4);
+                    if constexpr (PAIR) {
+                        t[j][i] = *reinterpret_cast<const f32v4*>(row + min(xc, n - 2));
+                    } else {
+                        const float2 p = row[min(xc, n - 1)], q = row[min(xc + 1, n - 1)];
+                        t[j][i] = f32v4{p.x, p.y, q.x, q.y};
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int j = 0; j < BS; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    tile[j * (kTile / 2) + (i * 16 + lane / 4) * 4 + ((lane % 4) ^ (lane / 16))] = t[j][i];
+            __builtin_amdgcn_wave_barrier();
+            const int xe = min(x0 + kGyCols, xb);
+#pragma unroll 1
+            for (int x = x0; x < xe; ++x) {
+                const int q = (x - x0) / 2, h = (x - x0) % 2;
+                float2 g[BS];
+#pragma unroll
+                for (int j = 0; j < BS; ++j)
+                    g[j] = reinterpret_cast<const float2*>(tile)[2 * (j * (kTile / 2) + lane * 4 + (q ^ ((lane / 4) % 4))) + h];
+#pragma unroll
+                for (int c = 0; c < kKpMaxScales; ++c) {
+                    if (c < d.ns) {
+                        float2 z[F];
+                        load_planar<F>(z, d.Zt + ((long long)c * n + x) * n * F, n, ys);
+#pragma unroll
+                        for (int j = 0; j < BS; ++j) {
+                            float2 xv[F];
+                            load_uniform<F>(xv, d.XAt + (((long long)c * nbs + min(bs0 + j, nbs - 1)) * n + x) * F);
+#pragma unroll
+                            for (int f = 0; f < F; ++f) acc[j][c][f] = cjmad(cmul(z[f], xv[f]), g[j], acc[j][c][f]);
+                        }
+                    }
+                }
             }
         }
+        add_parts<F, BS, PARTS>(red, acc, wave, lane, d.gY, d.ns, nbs, bs0, n, y);
     }
 }
 
@@ -473,18 +504,18 @@ __global__ __launch_bounds__(kThreads) void k_kp_grad_y(const KPDesc d) {
 // (h and gqs, with far fewer outputs and a longer sum, are k_kp_chain_h's)
 __global__ __launch_bounds__(kThreads) void k_kp_chain1(const KPDesc d) {
     const int n = d.n, S = d.S, B = d.B, F = d.F;
-    const long long n_sn = (long long)d.ns * S * n * F;   // gXs, gYs
-    const long long n_bn = (long long)d.ns * B * n * F;   // gqx, gqy
-    const long long total = 2 * n_sn + 2 * n_bn;
-    for (long long e = gtid(); e < total; e += gstride()) {
+    const unsigned n_sn = (unsigned)d.ns * S * n * F;   // gXs, gYs
+    const unsigned n_bn = (unsigned)d.ns * B * n * F;   // gqx, gqy
+    const unsigned total = 2 * n_sn + 2 * n_bn;
+    for (unsigned e = gtid(); e < total; e += gstride()) {
         float2 acc = make_float2(0.f, 0.f);
         if (e < 2 * n_sn) {
             const bool isx = e < n_sn;
-            const long long r = isx ? e : e - n_sn;
+            const unsigned r = isx ? e : e - n_sn;
             const int f = (int)(r % F);
             const int i = (int)((r / F) % n);
-            const int s = (int)((r / ((long long)F * n)) % S);
-            const int c = (int)(r / ((long long)F * n * S));
+            const int s = (int)((r / ((unsigned)F * n)) % S);
+            const int c = (int)(r / ((unsigned)F * n * S));
             const float2 a = d.params[d.a_off + f];
             for (int b = 0; b < B; ++b) {
                 const long long cbs = ((long long)c * B + b) * S + s;
@@ -495,13 +526,13 @@ __global__ __launch_bounds__(kThreads) void k_kp_chain1(const KPDesc d) {
             }
             (isx ? d.gXs : d.gYs)[r] = acc;
         } else if (e < 2 * n_sn + 2 * n_bn) {
-            const long long e2 = e - 2 * n_sn;
+            const unsigned e2 = e - 2 * n_sn;
             const bool isx = e2 < n_bn;
-            const long long r = isx ? e2 : e2 - n_bn;
+            const unsigned r = isx ? e2 : e2 - n_bn;
             const int f = (int)(r % F);
             const int i = (int)((r / F) % n);
-            const int b = (int)((r / ((long long)F * n)) % B);
-            const int c = (int)(r / ((long long)F * n * B));
+            const int b = (int)((r / ((unsigned)F * n)) % B);
+            const int c = (int)(r / ((unsigned)F * n * B));
             const float2 a = d.params[d.a_off + f];
             for (int s = 0; s < S; ++s) {
                 const long long cbs = ((long long)c * B + b) * S + s;
@@ -630,7 +661,7 @@ __device__ float2 reg_grad(const KPDesc& d, int c, int pl, int i0, int i1, int f
 // regulariser gradient -> grad.
 __global__ __launch_bounds__(kThreads) void k_kp_grid(const KPDesc d) {
     const int n = d.n, S = d.S, F = d.F;
-    for (long long e = gtid(); e < d.n_params; e += gstride()) {
+    for (unsigned e = gtid(); e < d.n_params; e += gstride()) {
         int c, pl;
         long long idx;
         locate(d, e, &c, &pl, &idx);
@@ -640,9 +671,10 @@ __global__ __launch_bounds__(kThreads) void k_kp_grid(const KPDesc d) {
         }
         int d0, d1;
         grid_dims(d, c, pl, &d0, &d1);
-        const int f = (int)(idx % F);
-        const int i1 = (int)((idx / F) % d1);
-        const int i0 = (int)(idx / ((long long)F * d1));
+        const unsigned ix = (unsigned)idx;
+        const int f = (int)(ix % F);
+        const int i1 = (int)((ix / F) % d1);
+        const int i0 = (int)(ix / ((unsigned)F * d1));
         const int* tp = d.tr_ptr + c * (n + 1);
         float2 acc = make_float2(0.f, 0.f);
         switch (pl) {
@@ -694,14 +726,15 @@ __global__ __launch_bounds__(kThreads) void k_kp_reg_value(const KPDesc d) {
         return q / (sqrt(q + e2) + ep);
     };
     double acc = 0.0;
-    for (long long e = gtid(); e < d.a_off; e += gstride()) {
+    for (unsigned e = gtid(); e < d.a_off; e += gstride()) {
         int c, pl;
         long long idx;
         locate(d, e, &c, &pl, &idx);
         int d0, d1;
         grid_dims(d, c, pl, &d0, &d1);
-        const int i1 = (int)((idx / d.F) % d1);
-        const int i0 = (int)(idx / ((long long)d.F * d1));
+        const unsigned ix = (unsigned)idx;
+        const int i1 = (int)((ix / d.F) % d1);
+        const int i0 = (int)(ix / ((unsigned)d.F * d1));
         const long long s0 = (long long)d1 * d.F, s1 = d.F;
         const float2* p = d.params + e;
         const bool time = pl == KP_XT || pl == KP_YT || pl == KP_ST;
@@ -739,7 +772,7 @@ __global__ __launch_bounds__(kThreads) void k_kp_update(const KPDesc d) {
         inv_bc2s = 1.f / sqrtf(bc2);
     }
     float2* p = const_cast<float2*>(d.params);
-    for (long long e = gtid(); e < d.n_params; e += gstride()) {
+    for (unsigned e = gtid(); e < d.n_params; e += gstride()) {
         const float2 g = d.grad[e], v0 = p[e];
         if (adam) {
             float2 m = d.m[e], v = d.v[e];
@@ -764,15 +797,16 @@ __global__ void k_kp_advance(int* step) {
 }
 
 // proj / water / fat of vol [B][S][n][n]
+template <typename Ix>
 __global__ __launch_bounds__(kThreads) void k_kp_render(const KPDesc d, int split, float2* proj, float2* water,
                                                         float2* fat) {
     const long long nn = (long long)d.n * d.n;
-    const long long total = (long long)d.B * nn;
-    for (long long e = gtid(); e < total; e += gstride()) {
-        const long long b = e / nn, px = e % nn;
+    const Ix total = (Ix)(d.B * nn);
+    for (Ix e = gtid(); e < total; e += gstride()) {
+        const Ix b = e / (Ix)nn, px = e % (Ix)nn;
         float2 w = make_float2(0.f, 0.f), ft = w;
         for (int s = 0; s < d.S; ++s) {
-            const float2 v = d.vol[(b * d.S + s) * nn + px];
+            const float2 v = d.vol[((long long)b * d.S + s) * nn + px];
             if (s < split) w = cadd(w, v);
             else ft = cadd(ft, v);
         }
@@ -781,6 +815,11 @@ __global__ __launch_bounds__(kThreads) void k_kp_render(const KPDesc d, int spli
         if (fat) fat[e] = ft;
     }
 }
+
+// The kernel over `total` elements with the index type that they need.
+#define KP_IX(KERNEL, TOTAL, ...)                                                                                   \
+    if ((TOTAL) >> 31) hipLaunchKernelGGL(KERNEL<unsigned long long>, dim3(grid_of(TOTAL)), dim3(kThreads), 0, s, __VA_ARGS__); \
+    else hipLaunchKernelGGL(KERNEL<unsigned>, dim3(grid_of(TOTAL)), dim3(kThreads), 0, s, __VA_ARGS__)
 
 inline unsigned grid_of(long long total) {
     const long long g = (total + kThreads - 1) / kThreads;
@@ -794,9 +833,10 @@ bool kp_features_ok(int f) { return f == 1 || f == 2 || f == 4 || f == 8 || f ==
 hipError_t kp_launch_factors(const KPDesc& d, hipStream_t s) {
     const dim3 b(kThreads);
     hipLaunchKernelGGL(k_kp_fac_s, dim3(grid_of((long long)d.ns * d.S * d.n * d.F)), b, 0, s, d);
-    hipLaunchKernelGGL(k_kp_fac_t, dim3(grid_of((long long)d.ns * d.B * (d.n + d.S) * d.F)), b, 0, s, d);
-    hipLaunchKernelGGL(k_kp_fac_z, dim3(grid_of((long long)d.ns * d.n * d.n * d.F)), b, 0, s, d);
-    hipLaunchKernelGGL(k_kp_prod, dim3(grid_of((long long)d.ns * d.B * d.S * d.n * d.F)), b, 0, s, d);
+    const long long nt = (long long)d.ns * d.B * (d.n + d.S) * d.F, np = (long long)d.ns * d.B * d.S * d.n * d.F;
+    KP_IX(k_kp_fac_t, nt, d);
+    hipLaunchKernelGGL(k_kp_fac_z, dim3(grid_of((d.Zt ? 2LL : 1LL) * d.ns * d.n * d.n * d.F)), b, 0, s, d);
+    KP_IX(k_kp_prod, np, d);
     return hipGetLastError();
 }
 
@@ -810,29 +850,46 @@ hipError_t kp_launch_factors(const KPDesc& d, hipStream_t s) {
         default: return hipErrorInvalidValue;                                       \
     }
 
+inline unsigned blocks_of(long long items) { return (unsigned)(items > (1 << 20) ? (1 << 20) : items); }
+
 hipError_t kp_launch_decode(const KPDesc& d, hipStream_t s) {
-    KP_F_SWITCH(k_kp_decode, dim3(grid_of((long long)d.B * ((d.S + kDecBins - 1) / kDecBins) * ((d.n + kDecRows - 1) / kDecRows) * ((d.n + 63) / 64) * 64)));
+    const long long items = (long long)d.B * ((d.S + 2 * kDecBins - 1) / (2 * kDecBins)) *
+                            ((d.n + 2 * kDecRows - 1) / (2 * kDecRows)) * ((d.n + 63) / 64);
+    KP_F_SWITCH(k_kp_decode, dim3(blocks_of(items)));
     return hipGetLastError();
 }
 
 hipError_t kp_launch_back_z(const KPDesc& d, hipStream_t s) {
-    KP_F_SWITCH(k_kp_grad_z, dim3(grid_of((long long)d.zchunks * ((d.n + kGzRows - 1) / kGzRows) * ((d.n + 63) / 64) * 64)));
+    const long long items = (long long)d.zchunks * ((d.n + 4 * kGzRows - 1) / (4 * kGzRows)) * ((d.n + 63) / 64);
+    KP_F_SWITCH(k_kp_grad_z, dim3(blocks_of(items)));
     hipLaunchKernelGGL(k_kp_grad_z_sum, dim3(grid_of((long long)d.ns * d.n * d.n * d.F)), dim3(kThreads), 0, s, d);
     return hipGetLastError();
 }
-hipError_t kp_launch_back_x(const KPDesc& d, hipStream_t s) {
-    KP_F_SWITCH(k_kp_grad_x, dim3(grid_of((long long)((d.B * d.S + kGxBs - 1) / kGxBs) * ((d.n + 63) / 64) * 64 * kGxYs)));
-    hipLaunchKernelGGL(k_kp_gx_sum, dim3(grid_of((long long)d.ns * d.B * d.S * d.n * d.F)), dim3(kThreads), 0, s, d);
-    return hipGetLastError();
-}
+// Features FF on the shape that kp_one_bs chooses, `parts` waves a block with two (b, s) a wave.
+#define KP_GX(KERNEL, FF, PARTS, ...)                                                                             \
+    case FF:                                                                                                      \
+        if (kp_one_bs(d)) hipLaunchKernelGGL((KERNEL<FF, 1, kWideParts __VA_OPT__(,) __VA_ARGS__>),               \
+                                             dim3(blocks_of(nseg * nbs)), dim3(64 * kWideParts), 0, s, d);        \
+        else hipLaunchKernelGGL((KERNEL<FF, (FF > 8 ? 1 : 2), PARTS __VA_OPT__(,) __VA_ARGS__>),                    \
+                                dim3(blocks_of(nseg * ((nbs + 1) / 2))), dim3(64 * PARTS), 0, s, d);              \
+        break
+#define KP_GX_SWITCH(KERNEL, PARTS, ...)                                                                      \
+    const long long nseg = (d.n + 63) / 64, nbs = (long long)d.B * d.S;                                       \
+    switch (d.F) {                                                                                            \
+        KP_GX(KERNEL, 1, PARTS __VA_OPT__(,) __VA_ARGS__); KP_GX(KERNEL, 2, PARTS __VA_OPT__(,) __VA_ARGS__); \
+        KP_GX(KERNEL, 4, PARTS __VA_OPT__(,) __VA_ARGS__); KP_GX(KERNEL, 8, PARTS __VA_OPT__(,) __VA_ARGS__); \
+        KP_GX(KERNEL, 16, PARTS __VA_OPT__(,) __VA_ARGS__);                                                   \
+        default: return hipErrorInvalidValue;                                                                 \
+    }                                                                                                         \
+    return hipGetLastError()
+
+hipError_t kp_launch_back_x(const KPDesc& d, hipStream_t s) { KP_GX_SWITCH(k_kp_grad_x, kGxParts); }
 hipError_t kp_launch_back_y(const KPDesc& d, hipStream_t s) {
-    // as the kernel's blocks of RB (b, s) by RY rows, RB RY = 32 / F
-    const int rw = 32 / d.F, ry = rw >= 16 ? 4 : (rw >= 4 ? 2 : 1), rb = rw / ry;
-    const long long groups = ((long long)(d.B * d.S + rb - 1) / rb) * ((d.n + ry - 1) / ry);
-    const long long blocks = (groups + kThreads / 64 - 1) / (kThreads / 64);
-    KP_F_SWITCH(k_kp_grad_y, dim3((unsigned)(blocks > (1 << 20) ? (1 << 20) : blocks)));
-    return hipGetLastError();
+    if ((d.n & 1) == 0 && ((uintptr_t)d.G & 15) == 0) { KP_GX_SWITCH(k_kp_grad_y, kGyParts, true); }
+    KP_GX_SWITCH(k_kp_grad_y, kGyParts, false);
 }
+#undef KP_GX_SWITCH
+#undef KP_GX
 hipError_t kp_launch_back(const KPDesc& d, hipStream_t s) {
     hipError_t e = kp_launch_back_z(d, s);
     if (e == hipSuccess) e = kp_launch_back_x(d, s);
@@ -867,8 +924,8 @@ hipError_t kp_launch_reg_value(const KPDesc& d, hipStream_t s) {
 }
 
 hipError_t kp_launch_render(const KPDesc& d, int split, float2* proj, float2* water, float2* fat, hipStream_t s) {
-    hipLaunchKernelGGL(k_kp_render, dim3(grid_of((long long)d.B * d.n * d.n)), dim3(kThreads), 0, s, d, split, proj,
-                       water, fat);
+    const long long total = (long long)d.B * d.n * d.n;
+    KP_IX(k_kp_render, total, d, split, proj, water, fat);
     return hipGetLastError();
 }
 

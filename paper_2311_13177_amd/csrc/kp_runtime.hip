@@ -179,11 +179,13 @@ hipError_t kp_device(KPTables* t, DevArena* ar, bool with_grad, hipStream_t s) {
     ok(ar->alloc(&d.Yf, ns * B * S * n * F));
     if (with_grad) {
         ok(ar->alloc(&d.gZ, ns * n * n * F));
-        // enough (b, s) chunks for about 4096 wave tasks (two rows by 64 columns) in the
-        // xy-gradient pass
-        d.zchunks = (int)std::max<size_t>(1, std::min<size_t>(B * S, (524288 + n * n - 1) / (n * n)));
+        // as many (b, s) chunks as make one round of the xy-gradient pass's blocks, four per CU
+        // (eight rows by 64 columns each)
+        d.zchunks = (int)std::max<size_t>(1, std::min<size_t>(B * S, 1024 / (((n + 63) / 64) * ((n + 7) / 8))));
+        ok(ar->alloc(&d.Zt, ns * n * n * F));
+        ok(ar->alloc(&d.XAt, ns * B * S * n * F));
         ok(ar->alloc(&d.zpart, (size_t)d.zchunks * ns * n * n * F));
-        ok(ar->alloc(&d.gXA, 2 * ns * B * S * n * F));
+        ok(ar->alloc(&d.gXA, ns * B * S * n * F));
         ok(ar->alloc(&d.gY, ns * B * S * n * F));
         ok(ar->alloc(&d.gXs, ns * S * n * F));
         ok(ar->alloc(&d.gYs, ns * S * n * F));

@@ -51,10 +51,12 @@ struct KPDesc {
     float2 *Xs, *Ys;     // [ns][S][n][F]
     float2 *qx, *qy;     // [ns][B][n][F]
     float2* qs;          // [ns][B][S][F]
-    float2* Z;           // [ns][n][n][F]
-    float2 *XA, *Yf;     // [ns][B][S][n][F]
-    float2 *gZ, *gY;
-    float2* gXA;         // [2][ns][B][S][n][F]: row-range partial sums, summed into part 0
+    float2* Z;           // [ns][n][F / 2][n][2]: rows y, feature-planar over x
+    float2* Zt;          // the same with rows x, over y (gradients only, else nullptr)
+    float2* XA;          // [ns][B][S][F / 2][n][2]
+    float2* XAt;         // [ns][B][S][n][F] (gradients only)
+    float2* Yf;          // [ns][B][S][n][F]
+    float2 *gZ, *gY, *gXA;  // [ns][n][n][F], [ns][B][S][n][F]
     float2* zpart;       // [zchunks][ns][n][n][F] partial sums of gZ over (b, s) chunks
     int zchunks;
     float2 *gXs, *gYs, *gqx, *gqy, *gqs, *h;  // h: [ns][B][S][F]
