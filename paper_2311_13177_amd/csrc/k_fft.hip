@@ -169,10 +169,9 @@ __host__ __device__ constexpr int ct_radix(int n, int i) {
     return 0;
 }
 
-template <int DIR, int R, bool FFAST, int N, int COUNT, int P>
+template <int DIR, int R, bool FFAST, int N, int COUNT, int P, int FS, int ES>
 __device__ __forceinline__ void ct_stage(float2* buf, const float2* tw, int tid) {
     constexpr int m = N / R, total = m * COUNT, tws = N / (P * R);
-    constexpr int FS = FFAST ? 1 : N, ES = FFAST ? COUNT : 1;
     constexpr int MAXB = (total + kThreads - 1) / kThreads;
     float2 x[MAXB][R];
     int bout[MAXB];
@@ -208,12 +207,13 @@ __device__ __forceinline__ void ct_stage(float2* buf, const float2* tw, int tid)
     __syncthreads();
 }
 
-template <int DIR, bool FFAST, int N, int COUNT, int ST = 0, int P = 1>
+// FS, ES: distances of neighbouring transforms and of a transform's neighbouring elements.
+template <int DIR, bool FFAST, int N, int COUNT, int FS = FFAST ? 1 : N, int ES = FFAST ? COUNT : 1, int ST = 0, int P = 1>
 __device__ __forceinline__ void ct_fft(float2* buf, const float2* tw, int tid) {
     if constexpr (ct_radix(N, ST) != 0) {
         constexpr int R = ct_radix(N, ST);
-        ct_stage<DIR, R, FFAST, N, COUNT, P>(buf, tw, tid);
-        ct_fft<DIR, FFAST, N, COUNT, ST + 1, P * R>(buf, tw, tid);
+        ct_stage<DIR, R, FFAST, N, COUNT, P, FS, ES>(buf, tw, tid);
+        ct_fft<DIR, FFAST, N, COUNT, FS, ES, ST + 1, P * R>(buf, tw, tid);
     }
 }
 
@@ -531,6 +531,144 @@ __global__ __launch_bounds__(kThreads) void k_cols(const KArgs a) {
     }
 }
 
+// ------------------------------------------------------------------ whole blades
+//
+// The row and column passes of one blade in one block, the blade in LDS between them: COL_STEP is
+// the forward rows, the column pass and the inverse rows, COL_FORWARD the first two, COL_ADJOINT
+// the last two. Group g of 256 threads does what the passes' items of rows and of columns 16 g ..
+// 16 g + 15 do, in the same order, so the results (loss partials too) are the same bits.
+// For lengths up to kBladeN, where a pass has at most four items per blade and its time is that
+// of a launch and of a trip through memory. Bound by the chain of stages through LDS (24 barriers)
+// of one block per CU. (Five blades of 64^2: 15 us in three launches, 11 us here, and two launches
+// fewer a step.)
+template <int NC>
+__global__ __launch_bounds__(4 * kThreads) void k_blade(const KArgs a) {
+    extern __shared__ float2 sm[];
+    __shared__ float red[16];
+    const int slice = 0, b = blockIdx.x;
+    int* const stepp = DF(step);
+    const int st = read_step(stepp);
+    if (stepp && st >= DF(step_limit)) return;
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), tid = threadIdx.x % kThreads;
+    const int n = NC > 0 ? NC : DF(n), nparts = DF(nparts), nstage = DF(nstage), code = DF(radix_code);
+    float* const loss = DF(loss_part) + b * DF(n_col_items) + g;
+    if (!active_blade(DF(schedule), DF(sched_seed), stepp, st, DF(B), b)) {
+        if (a.mode == COL_STEP && tid == 0) *loss = 0.f;
+        return;
+    }
+    const int pitch = blade_pitch(n), g0 = g * 16, ne = 16 * n;
+    const float ninv = 1.0f / (float)n;
+    const size_t nn = (size_t)n * n;
+    float2* const tw = sm + 16 * blade_groups(n) * pitch;
+    float2* const R = sm + g0 * pitch;  // the group's rows
+    float2* const C = sm + g0;          // the group's columns
+    float2* const img = DF(work) + (size_t)b * nparts * nn;
+    const float2* const twg = DF(tw);
+    for (int i = threadIdx.x; i < n; i += blockDim.x) tw[i] = twg[i];
+    // a thread's values of the group's rows and of its columns (ne <= 4 kThreads)
+    auto row_at = [&](int i, int* r, int* x) {
+        const int k = small_div(i, ninv);
+        *r = g0 + k;
+        *x = i - k * n;
+    };
+    const bool adj = a.mode == COL_ADJOINT;
+    float2 yr[4];
+    uint8_t mr[4];
+    const uint8_t* const mk = DF(mask) + (size_t)b * nn;
+    const float2* const yy = adj ? a.in0 : DF(y);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i = tid + k * kThreads, y = i >> 4, c = g0 + (i & 15);
+        yr[k] = make_float2(0.f, 0.f);
+        mr[k] = 0;
+        if (i < ne && c < n) {
+            mr[k] = mk[y * n + c];
+            if (yy) yr[k] = yy[(size_t)b * nn + y * n + c];
+        }
+    }
+    const float sc = 1.0f / (float)n;
+    if (adj) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = tid + k * kThreads;
+            if (i < ne) C[(i >> 4) * pitch + (i & 15)] = mr[k] != 0 ? cscale(yr[k], sc) : make_float2(0.f, 0.f);
+        }
+        __syncthreads();
+    } else {
+        const AS4 BladeDev* bd = cst(DF(blade)) + b;
+        const bool two = nparts == 2, has0 = !two || bd->has0, has1 = two && bd->has1;
+        float2 p0[4], p1[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            int r, x;
+            row_at(tid + k * kThreads, &r, &x);
+            p0[k] = p1[k] = make_float2(0.f, 0.f);
+            if (tid + k * kThreads < ne && r < n) {
+                if (has0) p0[k] = img[r * n + x];
+                if (has1) p1[k] = img[nn + r * n + x];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            int r, x;
+            row_at(tid + k * kThreads, &r, &x);
+            float2 v = p0[k];
+            if (two) {
+                if (has0) v = cscale(v, bd->w0);
+                if (has1) v = cfma(bd->w1, p1[k], v);
+                if (r >= n) v = make_float2(0.f, 0.f);
+            }
+            if (tid + k * kThreads < ne) sm[r * pitch + x] = v;
+        }
+        __syncthreads();
+        if constexpr (NC != 0) {
+            ct_fft<-1, false, NC, 16, blade_pitch(NC), 1>(R, tw, tid);
+            ct_fft<-1, true, NC, 16, 1, blade_pitch(NC)>(C, tw, tid);
+        } else {
+            lds_fft<-1, false, 4>(R, tw, n, 16, pitch, 1, nstage, code, tid);
+            lds_fft<-1, true, 4>(C, tw, n, 16, 1, pitch, nstage, code, tid);
+        }
+        const float dw = a.mode == COL_STEP ? DF(data_w) : 1.0f;
+        const float sc_res = dw * sc;
+        float lsum = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int i = tid + k * kThreads, y = i >> 4, c = g0 + (i & 15);
+            if (i < ne && c < n) {
+                float2* const p = C + y * pitch + (i & 15);
+                float2 r = make_float2(0.f, 0.f);
+                if (mr[k] != 0) r = csub(cscale(*p, sc), yr[k]);
+                if (a.mode == COL_FORWARD) {
+                    a.out0[(size_t)b * nn + y * n + c] = r;
+                } else {
+                    lsum = __builtin_fmaf(r.x, r.x, lsum);
+                    lsum = __builtin_fmaf(r.y, r.y, lsum);
+                    *p = cscale(r, sc_res);
+                }
+            }
+        }
+        if (a.mode == COL_FORWARD) return;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+        if ((tid & 63) == 0) red[4 * g + (tid >> 6)] = lsum;
+        __syncthreads();
+        if (tid == 0) *loss = dw * ((red[4 * g] + red[4 * g + 1]) + (red[4 * g + 2] + red[4 * g + 3]));
+    }
+    if constexpr (NC != 0) {
+        ct_fft<1, true, NC, 16, 1, blade_pitch(NC)>(C, tw, tid);
+        ct_fft<1, false, NC, 16, blade_pitch(NC), 1>(R, tw, tid);
+    } else {
+        lds_fft<1, true, 4>(C, tw, n, 16, 1, pitch, nstage, code, tid);
+        lds_fft<1, false, 4>(R, tw, n, 16, pitch, 1, nstage, code, tid);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        int r, x;
+        row_at(tid + k * kThreads, &r, &x);
+        if (tid + k * kThreads < ne && r < n) img[r * n + x] = sm[r * pitch + x];
+    }
+}
+
 // ------------------------------------------------------------------ launchers
 
 static inline int grid_for(int ntasks) { return ntasks < 1 ? 1 : (ntasks > (1 << 20) ? (1 << 20) : ntasks); }
@@ -573,6 +711,14 @@ hipError_t launch_cols(const KArgs& a, int n, size_t lds, hipStream_t s) {
         default: CV(0);
     }
 #undef CV
+    return hipGetLastError();
+}
+
+hipError_t launch_blades(const KArgs& a, hipStream_t s) {
+    const int n = a.one.n, g = blade_groups(n);
+    const size_t lds = ((size_t)16 * g * blade_pitch(n) + n) * sizeof(float2);
+    if (n == 64) hipLaunchKernelGGL((k_blade<64>), dim3(a.one.B), dim3(g * kThreads), lds, s, a);
+    else hipLaunchKernelGGL((k_blade<0>), dim3(a.one.B), dim3(g * kThreads), lds, s, a);
     return hipGetLastError();
 }
 

@@ -245,18 +245,17 @@ hipError_t dense_forward(const DenseStep& ds, hipStream_t s) {
     hipError_t e;
     a.tasks = L.proj; a.ntasks = L.n_proj;
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, s)) != hipSuccess) return e;
-    a.tasks = L.rows; a.ntasks = L.n_rows;
-    if ((e = launch_rows(a, -1, L.fft_n, L.lds_rows, s)) != hipSuccess) return e;
-    a.tasks = L.cols; a.ntasks = L.n_cols; a.mode = COL_STEP;
-    return launch_cols(a, L.fft_n, L.lds_cols, s);
+    return launch_blur(a, L, COL_STEP, false, s);
 }
 
 hipError_t dense_adjoint(const DenseStep& ds, hipStream_t s) {
     KArgs a = ds.a;
     const StageLists& L = ds.L;
     hipError_t e;
-    a.tasks = L.rows; a.ntasks = L.n_rows;
-    if ((e = launch_rows(a, 1, L.fft_n, L.lds_rows, s)) != hipSuccess) return e;
+    if (!blades_whole(a, L)) {  // else the forward has gone back through the rows
+        a.tasks = L.rows; a.ntasks = L.n_rows;
+        if ((e = launch_rows(a, 1, L.fft_n, L.lds_rows, s)) != hipSuccess) return e;
+    }
     a.tasks = L.gath; a.ntasks = L.n_gath; a.accumulate = 0;
     return launch_gather_lists(a, GATHER_STORE, L, s);
 }

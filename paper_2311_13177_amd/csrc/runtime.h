@@ -17,6 +17,8 @@ hipError_t launch_project(const KArgs& a, int rows, int gw, int waves, int re, b
 // n: the length of every slice of the launch, or kFftMixed (lds: the largest over the slices).
 hipError_t launch_rows(const KArgs& a, int dir, int n, size_t lds, hipStream_t s);
 hipError_t launch_cols(const KArgs& a, int n, size_t lds, hipStream_t s);
+// Every blade of one slice (a.one) through the passes of a.mode, one block each (n <= kBladeN).
+hipError_t launch_blades(const KArgs& a, hipStream_t s);
 // Whether a length has compile-time passes.
 bool fft_compiled(int n);
 // waves: 4 or 8 per work item (the layout's gath_w: its bin chunks hold waves * sc bins)
@@ -62,6 +64,14 @@ struct StageLists {
     int epi = EPI_GENERIC;         // optimiser epilogue every slice of the step can take
     int stream = 0;                // the step's state exceeds kStreamState (EPI_STREAM)
 };
+
+// Whether a launch's row and column passes are one (launch_blades): one slice of a small length.
+inline bool blades_whole(const KArgs& a, const StageLists& L) {
+    return !a.descs && L.segs.empty() && L.fft_n <= kBladeN;
+}
+// One slice's row and column passes: COL_STEP (work to work; without `back` the inverse rows may be
+// left out), COL_FORWARD (work to a.out0) or COL_ADJOINT (a.in0 to work).
+hipError_t launch_blur(KArgs a, const StageLists& L, int mode, bool back, hipStream_t s);
 
 StageLists plan_lists(const vp_plan* p, const DeviceTables* t, const Layout* L, const DeviceLayout* dl);
 // Whether a step over `voxels` voxels (summed over its slices) streams its state.

@@ -284,6 +284,21 @@ vp_status check_options(const vp_plan* p, const vp_options* o) {
 
 // ------------------------------------------------------------------ launch sequences
 
+hipError_t launch_blur(KArgs a, const StageLists& L, int mode, bool back, hipStream_t s) {
+    a.mode = mode;
+    if (blades_whole(a, L)) return launch_blades(a, s);
+    hipError_t e = hipSuccess;
+    auto rows = [&](int dir) {
+        a.tasks = L.rows; a.ntasks = L.n_rows;
+        if (e == hipSuccess) e = launch_rows(a, dir, L.fft_n, L.lds_rows, s);
+    };
+    if (mode != COL_ADJOINT) rows(-1);
+    a.tasks = L.cols; a.ntasks = L.n_cols;
+    if (e == hipSuccess) e = launch_cols(a, L.fft_n, L.lds_cols, s);
+    if (mode == COL_ADJOINT || (mode == COL_STEP && back)) rows(1);
+    return e;
+}
+
 void launch_step(const KArgs& base, const StageLists& L, hipStream_t s, hipError_t* err, hipEvent_t* ev) {
     // the projection takes the step counters' snapshot and the step's last kernel advances
     // them from it: both launches must have work items (every plan has, by construction)
@@ -318,15 +333,17 @@ void launch_step(const KArgs& base, const StageLists& L, hipStream_t s, hipError
         }
         return true;
     };
-    if (!rows(-1)) { *err = e; return; }
+    const bool whole = blades_whole(a, L);
+    if (!whole && !rows(-1)) { *err = e; return; }
     MARK(2);
     a.mode = COL_STEP;
-    for (int i = 0; i < nseg; ++i) {
+    if (whole && (e = launch_blades(a, s)) != hipSuccess) { *err = e; return; }
+    for (int i = 0; i < nseg && !whole; ++i) {
         a.tasks = L.cols + segs[i].cols0; a.ntasks = segs[i].n_cols;
         if ((e = launch_cols(a, segs[i].n, segs[i].lds_cols, s)) != hipSuccess) { *err = e; return; }
     }
     MARK(3);
-    if (!rows(1)) { *err = e; return; }
+    if (!whole && !rows(1)) { *err = e; return; }
     MARK(4);
     a.tasks = L.gath; a.ntasks = L.n_gath;
     a.snap = 1;
@@ -429,11 +446,8 @@ extern "C" vp_status vp_forward(const vp_plan* p, const vp_c64* d_vol, const vp_
     a.tasks = L.proj; a.ntasks = L.n_proj;
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, sc.s)) != hipSuccess)
         return hip_status(e, "vp_forward project");
-    a.tasks = L.rows; a.ntasks = L.n_rows;
-    if ((e = launch_rows(a, -1, L.fft_n, L.lds_rows, sc.s)) != hipSuccess) return hip_status(e, "vp_forward rows");
-    a.tasks = L.cols; a.ntasks = L.n_cols; a.mode = COL_FORWARD; a.out0 = (float2*)d_out;
-    if ((e = launch_cols(a, L.fft_n, L.lds_cols, sc.s)) != hipSuccess) return hip_status(e, "vp_forward cols");
-    return VP_OK;
+    a.out0 = (float2*)d_out;
+    return hip_status(launch_blur(a, L, COL_FORWARD, false, sc.s), "vp_forward DFT");
 }
 
 extern "C" vp_status vp_adjoint(const vp_plan* p, const vp_c64* d_kres, vp_c64* d_grad, int32_t accumulate,
@@ -450,10 +464,8 @@ extern "C" vp_status vp_adjoint(const vp_plan* p, const vp_c64* d_kres, vp_c64* 
     a.accumulate = accumulate != 0;
     const StageLists L = plan_lists(p, sc.t, sc.lay, sc.dl);
     hipError_t e;
-    a.tasks = L.cols; a.ntasks = L.n_cols; a.mode = COL_ADJOINT; a.in0 = (const float2*)d_kres;
-    if ((e = launch_cols(a, L.fft_n, L.lds_cols, sc.s)) != hipSuccess) return hip_status(e, "vp_adjoint cols");
-    a.tasks = L.rows; a.ntasks = L.n_rows;
-    if ((e = launch_rows(a, 1, L.fft_n, L.lds_rows, sc.s)) != hipSuccess) return hip_status(e, "vp_adjoint rows");
+    a.in0 = (const float2*)d_kres;
+    if ((e = launch_blur(a, L, COL_ADJOINT, true, sc.s)) != hipSuccess) return hip_status(e, "vp_adjoint DFT");
     a.tasks = L.gath; a.ntasks = L.n_gath;
     if ((e = launch_gather_lists(a, GATHER_STORE, L, sc.s)) != hipSuccess)
         return hip_status(e, "vp_adjoint gather");
@@ -545,11 +557,8 @@ extern "C" vp_status vp_forward_noalloc(const vp_plan* p, const vp_c64* d_vol, c
     a.tasks = L.proj; a.ntasks = L.n_proj;
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, s)) != hipSuccess)
         return hip_status(e, "vp_forward_noalloc project");
-    a.tasks = L.rows; a.ntasks = L.n_rows;
-    if ((e = launch_rows(a, -1, L.fft_n, L.lds_rows, s)) != hipSuccess) return hip_status(e, "vp_forward_noalloc rows");
-    a.tasks = L.cols; a.ntasks = L.n_cols; a.mode = COL_FORWARD; a.out0 = (float2*)d_out;
-    if ((e = launch_cols(a, L.fft_n, L.lds_cols, s)) != hipSuccess) return hip_status(e, "vp_forward_noalloc cols");
-    return VP_OK;
+    a.out0 = (float2*)d_out;
+    return hip_status(launch_blur(a, L, COL_FORWARD, false, s), "vp_forward_noalloc DFT");
 }
 
 // Section 6 baselines: the coverage-weighted average (scaled by 1/n) into d_out, then the
@@ -1279,10 +1288,7 @@ vp_status session_objective_enqueue(vp_session* s, hipStream_t stream) {
     a.tasks = L.proj; a.ntasks = L.n_proj;
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, stream)) != hipSuccess)
         return hip_status(e, "objective");
-    a.tasks = L.rows; a.ntasks = L.n_rows;
-    if ((e = launch_rows(a, -1, L.fft_n, L.lds_rows, stream)) != hipSuccess) return hip_status(e, "objective");
-    a.tasks = L.cols; a.ntasks = L.n_cols; a.mode = COL_STEP;
-    if ((e = launch_cols(a, L.fft_n, L.lds_cols, stream)) != hipSuccess) return hip_status(e, "objective");
+    if ((e = launch_blur(a, L, COL_STEP, false, stream)) != hipSuccess) return hip_status(e, "objective");
     a.tasks = L.vox; a.ntasks = L.n_vox; a.dpart = s->dpart;
     if ((e = launch_reg_value(a, stream)) != hipSuccess) return hip_status(e, "objective");
     const size_t nl = loss_slots(p), nd = 2 * p->t_vox.size();

@@ -77,6 +77,13 @@ __host__ __device__ constexpr int fft_rows_per_item(int n) { return 1024 / n < 1
 __host__ __device__ constexpr int fft_cols_per_item(int n) {
     return n == 512 ? 8 : (n > 256 ? 4 : (n == 256 || n == 192 ? 8 : 16));
 }
+// Lengths up to kBladeN have their whole blade transformed by one block (k_blade): at most four
+// groups of 256 threads, each the item of a row and of a column pass (16 rows, 16 columns). The
+// blade's rows are blade_pitch apart in LDS: 16 or 48 values modulo 64, so that 16 columns of two
+// neighbouring rows lie in different banks.
+constexpr int kBladeN = 64;
+__host__ __device__ constexpr int blade_pitch(int n) { return (n + 15) / 32 * 32 + 16; }
+__host__ __device__ constexpr int blade_groups(int n) { return (n + 15) / 16; }
 // Length argument of a DFT pass over several of the lengths up to 384 with a compile-time plan.
 constexpr int kFftMixed = -1;
 // LDS of a column item without the measurement and mask strips (the raw passes)

@@ -49,3 +49,29 @@ def test_batches_of_mixed_lengths_equal_solo_fits(gpu_lib, lengths):
     for p, y, g in zip(plans, ys, got):
         want = B.vp_reconstruct(p, y, opts)
         assert np.array_equal(g["vol"], want["vol"]) and g["final_loss"] == want["final_loss"]
+
+
+# one block per blade against the separate passes, which a batch takes: one to four groups of 16
+# rows and columns, whole and partial, one and two knots a blade, steps that skip blades
+@pytest.mark.parametrize("n", [5, 16, 18, 32, 36, 45, 48, 50, 64])
+@pytest.mark.parametrize("n_time,schedule", [(1, "all"), (3, "all"), (3, "cyclic"), (2, "random")])
+def test_whole_blades_equal_the_passes(gpu_lib, n, n_time, schedule):
+    import torch
+    from paper_2311_13177_amd import binding as B
+
+    case = configs.small_case(n=n, n_spec=2, n_time=n_time, n_blades=4, lines=min(5, n), f=0.5)
+    plan = B.Plan.from_geometry(case.geometry())
+    y = O.simulate_measurements(case)
+    sched = {"all": B.VP_SCHED_ALL_BLADES, "cyclic": B.VP_SCHED_CYCLIC, "random": B.VP_SCHED_RANDOM}[schedule]
+    opts = B.vp_options_default(n_steps=5, schedule=sched, seed=3)
+    (want,) = B.vp_batch_reconstruct([plan], [y], [opts])
+    got = B.vp_reconstruct(plan, y, opts)
+    assert np.array_equal(got["vol"], want["vol"]) and got["final_loss"] == want["final_loss"]
+    geom = O.Geometry.from_dict(case.geometry())
+    rng = np.random.default_rng(n)
+    vol = (rng.standard_normal(plan.volume_shape) + 1j * rng.standard_normal(plan.volume_shape)).astype(np.complex64)
+    d_y = torch.from_numpy(y).to("cuda")
+    k = B.vp_forward(plan, torch.from_numpy(vol).to("cuda"), d_y)
+    assert_close(k.cpu().numpy(), O.residual(vol.astype(np.complex128), geom, y.astype(np.complex128)), 1e-4)
+    g = B.vp_adjoint(plan, d_y).cpu().numpy()
+    assert_close(g, O.adjoint(y.astype(np.complex128), geom), 1e-4)
