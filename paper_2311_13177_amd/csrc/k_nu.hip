@@ -16,8 +16,8 @@ namespace vp {
 
 namespace {
 
-__device__ __forceinline__ long long gtid() { return (long long)blockIdx.x * blockDim.x + threadIdx.x; }
-__device__ __forceinline__ long long gstride() { return (long long)gridDim.x * blockDim.x; }
+__device__ __forceinline__ unsigned gtid() { return blockIdx.x * blockDim.x + threadIdx.x; }
+__device__ __forceinline__ unsigned gstride() { return gridDim.x * blockDim.x; }
 
 // Kernel value at offset u (grid units) from the table over [0, W/2]; 0 beyond W/2 (and
 // for NaN). Branch-free, so the loads of several lookups and of the data they weigh
@@ -31,7 +31,12 @@ __device__ __forceinline__ float kb(const float* tab, float u) {
     return in ? v : 0.f;
 }
 
-__device__ __forceinline__ int wrap(int m, int M) { return ((m % M) + M) % M; }
+// m modulo M. Grid positions stay within 0.71 M + 4 of the origin (|r|, |q| <= n / 2, M = 2 n), so
+// one correction is enough from M = 16 on.
+__device__ __forceinline__ int wrap(int m, int M) {
+    if (M < 16) return ((m % M) + M) % M;
+    return m < 0 ? m + M : (m >= M ? m - M : m);
+}
 
 // Sample (j, l) of blade b in grid units: kNuSigma (r u_b + q n_b), r = j - n/2,
 // q = l - L_b/2, in FP64 (exact to far below FP32's rounding of an offset). The
@@ -67,20 +72,19 @@ __global__ __launch_bounds__(kThreads) void k_nu_interp(const NuArgs d) {
     __shared__ float red[kThreads];
     float lsum = 0.f;
     const int n = d.n, M = d.M;
-    const long long per = (long long)d.lmax * n;
-    const long long total = (long long)d.B * per;
+    const unsigned per = (unsigned)d.lmax * n, total = d.B * per;  // at most 2^26
     const double h = 0.5 * (double)kNuWidth;
     const int sub = threadIdx.x % kRowLanes, slot = threadIdx.x / kRowLanes;
     const int st = read_step(d.stepp);
     // block-uniform loop: every lane reaches every barrier
-    for (long long base = (long long)blockIdx.x * kSamplesPerBlock; base < total;
-         base += (long long)gridDim.x * kSamplesPerBlock) {
-        const long long e = base + slot;
+    for (unsigned base = blockIdx.x * kSamplesPerBlock; base < total; base += gridDim.x * kSamplesPerBlock) {
+        const unsigned e = base + slot;
         int L = 0, b = 0, l = 0, j = 0;
         if (e < total) {
+            const unsigned r = e % per;
             b = (int)(e / per);
-            l = (int)((e % per) / n);
-            j = (int)(e % n);
+            l = (int)(r / n);
+            j = (int)(r % n);
             L = d.lines[b];
         }
         float2 acc = make_float2(0.f, 0.f);
@@ -143,19 +147,23 @@ __device__ __forceinline__ bool axis_range(double a, double ia, double bq, doubl
 // grid[b][gy][gx] = sum over the samples within W/2 (in both axes) of 2k - (gx, gy), at
 // every wrap of the grid point, of C C s conj(phase): the transpose of k_nu_interp. The
 // samples near a point are found from the lattice: the lines within reach, and on each
-// the readout interval that meets both axis windows.
+// the readout interval that meets both axis windows. A block's points are one blade's, so that
+// its angle and lines are scalars; a point's row is a product by the reciprocal of M (exact:
+// (p + 1/2) / M is at least 1 / (2 M) from a whole number and below 2^9). Bound by the arithmetic of
+// the points that have samples, about ten window tests and weights each: an FP32 test that drops
+// the others before the FP64 one gains nothing. (12 blades on 512^2: 41 us, 44 us with 64-bit
+// divisions for every point's indices; k_nu_interp 17 us, 18 us.)
 __global__ __launch_bounds__(kThreads) void k_nu_spread(const NuArgs d) {
-    const int n = d.n, M = d.M;
-    const long long MM = (long long)M * M;
-    const long long total = (long long)d.B * MM;
+    const int n = d.n, M = d.M, MM = M * M;
+    const float minv = 1.0f / (float)M;
     const double h = 0.5 * (double)kNuWidth;
     const double H = h / (double)kNuSigma;  // the window's half-width in lattice units
     const int st = read_step(d.stepp);
-    for (long long e = gtid(); e < total; e += gstride()) {
-        const int b = (int)(e / MM);
+    const int p = blockIdx.x * kThreads + threadIdx.x;
+    const int py = (int)(((float)p + 0.5f) * minv), px = p - py * M;
+    for (int b = blockIdx.y; b < d.B; b += gridDim.y) {
         // an inactive blade's grid is never read (its inverse passes and gather skip it)
-        if (!active_blade(d.sched, d.sseed, d.stepp, st, d.B, b)) continue;
-        const int py = (int)((e % MM) / M), px = (int)(e % M);
+        if (p >= MM || !active_blade(d.sched, d.sseed, d.stepp, st, d.B, b)) continue;
         const double2 cs = d.cs[b];
         const double c = cs.x, s = cs.y;
         const double ic = fabs(c) < 1e-12 ? 0.0 : 1.0 / c, is = fabs(s) < 1e-12 ? 0.0 : 1.0 / s;
@@ -188,15 +196,14 @@ __global__ __launch_bounds__(kThreads) void k_nu_spread(const NuArgs d) {
                 }
             }
         }
-        d.grid[e] = acc;
+        d.grid[(size_t)b * MM + p] = acc;
     }
 }
 
 // pre[b][l][j] = dw conj(phase) s_in (0 on lines l >= L_b)
 __global__ __launch_bounds__(kThreads) void k_nu_prep(const NuArgs d) {
-    const long long per = (long long)d.lmax * d.n;
-    const long long total = (long long)d.B * per;
-    for (long long e = gtid(); e < total; e += gstride()) {
+    const unsigned per = (unsigned)d.lmax * d.n, total = d.B * per;
+    for (unsigned e = gtid(); e < total; e += gstride()) {
         const int b = (int)(e / per), l = (int)((e % per) / d.n);
         float2 w = make_float2(0.f, 0.f);
         if (l < d.lines[b]) {
@@ -224,7 +231,7 @@ hipError_t nu_launch_prep(const NuArgs& d, hipStream_t s) {
     return hipGetLastError();
 }
 hipError_t nu_launch_spread(const NuArgs& d, hipStream_t s) {
-    hipLaunchKernelGGL(k_nu_spread, dim3(grid_of((long long)d.B * d.M * d.M)), dim3(kThreads), 0, s, d);
+    hipLaunchKernelGGL(k_nu_spread, dim3((d.M * d.M + kThreads - 1) / kThreads, d.B), dim3(kThreads), 0, s, d);
     return hipGetLastError();
 }
 
