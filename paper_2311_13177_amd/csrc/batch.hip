@@ -18,17 +18,8 @@
 namespace vp {
 
 SliceGroup::~SliceGroup() {
-    if (gexec) (void)hipGraphExecDestroy(gexec);
-    if (graph) (void)hipGraphDestroy(graph);
     if (d_descs) (void)hipFree(d_descs);
     if (d_tasks) (void)hipFree(d_tasks);
-}
-
-void SliceGroup::drop_graph() {
-    if (gexec) (void)hipGraphExecDestroy(gexec);
-    if (graph) (void)hipGraphDestroy(graph);
-    gexec = nullptr;
-    graph = nullptr;
 }
 
 // One tile shape for a whole group (the kernels take it as template parameters): the
@@ -71,7 +62,7 @@ static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
 
 // Builds descriptors and concatenated work lists for `sessions` (slice i = sessions[i]).
 vp_status group_build(SliceGroup* g, const std::vector<vp_session*>& sessions, const std::vector<int>& limits) {
-    g->drop_graph();
+    g->graph.drop();
     const int ns = (int)sessions.size();
     std::vector<SliceDesc>& descs = g->h_descs;
     descs.assign(ns, SliceDesc{});
@@ -183,25 +174,18 @@ vp_status group_build(SliceGroup* g, const std::vector<vp_session*>& sessions, c
     return VP_OK;
 }
 
-// Enqueues n_steps steps of every slice in the group; use_graph captures one step once.
+// Enqueues n_steps steps of every slice in the group; use_graph replays captured steps.
 vp_status group_run(SliceGroup* g, int n_steps, bool use_graph) {
     KArgs a{};
     a.descs = g->d_descs;
     hipError_t e;
     if (use_graph) {
-        if (!g->gexec) {
-            e = hipStreamBeginCapture(g->stream, hipStreamCaptureModeThreadLocal);
-            if (e != hipSuccess) return hip_status(e, "hipStreamBeginCapture");
+        e = g->graph.run(g->stream, n_steps, [&] {
             hipError_t le = hipSuccess;
             launch_step(a, g->lists, g->stream, &le);
-            e = hipStreamEndCapture(g->stream, &g->graph);
-            if (le != hipSuccess) return hip_status(le, "batched step capture");
-            if (e != hipSuccess) return hip_status(e, "hipStreamEndCapture");
-            e = hipGraphInstantiate(&g->gexec, g->graph, nullptr, nullptr, 0);
-            if (e != hipSuccess) return hip_status(e, "hipGraphInstantiate");
-        }
-        for (int i = 0; i < n_steps; ++i)
-            if ((e = hipGraphLaunch(g->gexec, g->stream)) != hipSuccess) return hip_status(e, "hipGraphLaunch");
+            return le;
+        });
+        if (e != hipSuccess) return hip_status(e, "batched step graph");
     } else {
         for (int i = 0; i < n_steps; ++i) {
             launch_step(a, g->lists, g->stream, &e);
@@ -231,7 +215,7 @@ struct vp_batch {
             (void)hipStreamSynchronize(g.stream);
         }
         owned.clear();
-        g.drop_graph();
+        g.graph.drop();
         if (g.stream) (void)hipStreamDestroy(g.stream);
         g.stream = nullptr;
     }

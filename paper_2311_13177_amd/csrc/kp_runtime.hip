@@ -380,12 +380,10 @@ struct vp_kplanes_session {
     float* loss_part = nullptr;
     int* step_dev = nullptr;
     int64_t steps_done = 0;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
+    vp::StepGraph graph;
     ~vp_kplanes_session() {
         if (stream) (void)hipStreamSynchronize(stream);
-        if (gexec) (void)hipGraphExecDestroy(gexec);
-        if (graph) (void)hipGraphDestroy(graph);
+        graph.drop();
         if (stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -500,22 +498,9 @@ extern "C" vp_status vp_kplanes_session_step(vp_kplanes_session* s, int32_t n_st
     if (n_steps < 0) return fail(VP_ERR_ARG, "vp_kplanes_session_step: n_steps < 0");
     hipError_t e = hipSetDevice(s->device);
     if (e != hipSuccess) return hip_status(e, "hipSetDevice");
-    if (use_graph && !s->gexec && n_steps > 0) {
-        e = hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal);
-        hipError_t le = hipSuccess;
-        if (e == hipSuccess) le = kp_step(s, nullptr);
-        hipGraph_t g = nullptr;
-        const hipError_t ce = hipStreamEndCapture(s->stream, &g);
-        if (e == hipSuccess) e = le != hipSuccess ? le : ce;
-        if (e == hipSuccess) e = hipGraphInstantiate(&s->gexec, g, nullptr, nullptr, 0);
-        if (e != hipSuccess) {
-            if (g) (void)hipGraphDestroy(g);
-            return hip_status(e, "vp_kplanes_session_step capture");
-        }
-        s->graph = g;
-    }
-    for (int i = 0; i < n_steps && e == hipSuccess; ++i)
-        e = use_graph ? hipGraphLaunch(s->gexec, s->stream) : kp_step(s, nullptr);
+    if (use_graph) e = s->graph.run(s->stream, n_steps, [&] { return kp_step(s, nullptr); });
+    else
+        for (int i = 0; i < n_steps && e == hipSuccess; ++i) e = kp_step(s, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_status(e, "vp_kplanes_session_step");
     s->steps_done += n_steps;

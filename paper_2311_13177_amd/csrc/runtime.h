@@ -102,6 +102,58 @@ static_assert(kCounterBytes >= (kSnapWord + 1) * sizeof(int), "counter block hol
 vp_status hip_status(hipError_t e, const char* what);
 vp_status check_options(const vp_plan* p, const vp_options* o);
 
+// The captured steps of a fit: a graph of one step and one of kMany. Between two graphs the GPU
+// idles for 8 us (static 64^2: 26 us of kernels in a step of 34 us), between the kernels of
+// one for none; eight steps a graph leave 1 us a step, and every count of steps is a few
+// graphs. The larger one is captured once a fit asks for 2 kMany steps in all: it costs about
+// what it saves by then.
+struct StepGraph {
+    static constexpr int kMany = 8;
+    hipGraph_t graph[2] = {nullptr, nullptr};
+    hipGraphExec_t exec[2] = {nullptr, nullptr};
+    int64_t replayed = 0;
+    ~StepGraph() { drop(); }
+    void drop() {
+        for (int i = 0; i < 2; ++i) {
+            if (exec[i]) (void)hipGraphExecDestroy(exec[i]);
+            if (graph[i]) (void)hipGraphDestroy(graph[i]);
+            exec[i] = nullptr;
+            graph[i] = nullptr;
+        }
+        replayed = 0;
+    }
+    // n steps on the stream; step() enqueues one (hipError_t).
+    template <typename F>
+    hipError_t run(hipStream_t s, int n, F step) {
+        hipError_t e = hipSuccess;
+        int left = n;
+        if (left >= kMany && (exec[1] || n + replayed >= 2 * kMany)) {
+            if (!exec[1]) e = capture(s, 1, kMany, step);
+            for (; e == hipSuccess && left >= kMany; left -= kMany) e = hipGraphLaunch(exec[1], s);
+        }
+        if (e == hipSuccess && left > 0 && !exec[0]) e = capture(s, 0, 1, step);
+        for (; e == hipSuccess && left > 0; --left) e = hipGraphLaunch(exec[0], s);
+        replayed += n;
+        return e;
+    }
+
+  private:
+    template <typename F>
+    hipError_t capture(hipStream_t s, int which, int steps, F step) {
+        hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+        if (e != hipSuccess) return e;
+        for (int i = 0; i < steps && e == hipSuccess; ++i) e = step();
+        const hipError_t ce = hipStreamEndCapture(s, &graph[which]);
+        if (e == hipSuccess) e = ce;
+        if (e == hipSuccess) e = hipGraphInstantiate(&exec[which], graph[which], nullptr, nullptr, 0);
+        if (e != hipSuccess && graph[which]) {
+            (void)hipGraphDestroy(graph[which]);
+            graph[which] = nullptr;
+        }
+        return e;
+    }
+};
+
 }  // namespace vp
 
 struct vp_session {
@@ -125,8 +177,7 @@ struct vp_session {
     float2* grad = nullptr;  // data gradient, allocated when a separate update pass runs
     void* h_part = nullptr;  // pinned objective partials (doubles, then loss floats)
     int64_t steps_done = 0;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
+    vp::StepGraph graph;
     vp::SliceDesc desc{};
     vp::StageLists lists{};
     ~vp_session();
@@ -145,17 +196,15 @@ struct SliceGroup {
     std::vector<SliceDesc> h_descs;       // host copies, kept until the stream has read them
     std::vector<Task> h_tasks;
     StageLists lists{};
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
+    StepGraph graph;
     ~SliceGroup();
-    void drop_graph();
 };
 // Builds descriptors and concatenated work lists for `sessions` (slice i = sessions[i],
 // stopping at limits[i] steps) and enqueues their upload on the group's stream (no
 // wait); drops any captured graph. Call it only once the stream has passed the previous
 // upload (the host copies are reused).
 vp_status group_build(SliceGroup* g, const std::vector<vp_session*>& sessions, const std::vector<int>& limits);
-// Enqueues n_steps steps of every slice of the group (use_graph: capture one step once).
+// Enqueues n_steps steps of every slice of the group (use_graph: replay captured steps).
 vp_status group_run(SliceGroup* g, int n_steps, bool use_graph);
 
 // Allocates and uploads a session on `stream` (nullptr: a stream of its own). The initial

@@ -779,14 +779,12 @@ struct vp_nu_session {
     float2* ys = nullptr;   // measured samples [B][Lmax][n]
     float* loss = nullptr;  // per-block sums of |residual|^2 of the last forward pass
     int nblk = 0;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
+    StepGraph graph;
     explicit vp_nu_session(vp_session* raw) : s(raw), nu(raw->stream, true) {}
     ~vp_nu_session() {
         (void)hipSetDevice(s->device);
         (void)hipStreamSynchronize(s->stream);
-        if (gexec) (void)hipGraphExecDestroy(gexec);
-        if (graph) (void)hipGraphDestroy(graph);
+        graph.drop();
         void* bufs[] = {res, ys, loss};
         for (void* q : bufs)
             if (q) (void)hipFree(q);
@@ -919,18 +917,10 @@ extern "C" vp_status vp_nu_session_step(vp_nu_session* x, int32_t n_steps, int32
     hipError_t e = hipSetDevice(x->s->device);
     if (e != hipSuccess) return hip_status(e, "hipSetDevice");
     const hipStream_t str = x->s->stream;
-    if (use_graph && n_steps > 1 && !x->gexec) {
-        e = hipStreamBeginCapture(str, hipStreamCaptureModeThreadLocal);
-        const hipError_t le = e == hipSuccess ? x->step(nullptr) : e;
-        hipGraph_t g = nullptr;
-        const hipError_t ce = hipStreamEndCapture(str, &g);
-        if (e == hipSuccess) e = le != hipSuccess ? le : ce;
-        x->graph = g;
-        if (e == hipSuccess) e = hipGraphInstantiate(&x->gexec, g, nullptr, nullptr, 0);
-        if (e != hipSuccess) return hip_status(e, "vp_nu_session_step capture");
-    }
-    for (int i = 0; i < n_steps && e == hipSuccess; ++i)
-        e = (use_graph && x->gexec) ? hipGraphLaunch(x->gexec, str) : x->step(nullptr);
+    // (a single step runs eagerly unless steps have been captured)
+    if (use_graph && (n_steps > 1 || x->graph.replayed > 0)) e = x->graph.run(str, n_steps, [&] { return x->step(nullptr); });
+    else
+        for (int i = 0; i < n_steps && e == hipSuccess; ++i) e = x->step(nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(str);
     if (e != hipSuccess) return hip_status(e, "vp_nu_session_step");
     x->s->steps_done += n_steps;
@@ -1122,8 +1112,7 @@ extern "C" vp_status vp_render(const vp_plan* p, const vp_c64* d_vol, int32_t sp
 
 vp_session::~vp_session() {
     if (device >= 0) (void)hipSetDevice(device);
-    if (gexec) (void)hipGraphExecDestroy(gexec);
-    if (graph) (void)hipGraphDestroy(graph);
+    graph.drop();
     if (stream) (void)hipStreamSynchronize(stream);
     void* ptrs[] = {vol[0], vol[1], m, v, work, y, loss_part, step_dev, dpart, render, grad};
     for (void* q : ptrs)
@@ -1234,21 +1223,12 @@ vp_status session_run(vp_session* s, int32_t n_steps, int32_t use_graph) {
     KArgs a{};
     a.one = s->desc;
     if (use_graph && n_steps > 1) {
-        if (!s->gexec) {
-            e = hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal);
-            if (e != hipSuccess) return hip_status(e, "hipStreamBeginCapture");
+        e = s->graph.run(s->stream, n_steps, [&] {
             hipError_t le = hipSuccess;
             launch_step(a, s->lists, s->stream, &le);
-            e = hipStreamEndCapture(s->stream, &s->graph);
-            if (le != hipSuccess) return hip_status(le, "step capture");
-            if (e != hipSuccess) return hip_status(e, "hipStreamEndCapture");
-            e = hipGraphInstantiate(&s->gexec, s->graph, nullptr, nullptr, 0);
-            if (e != hipSuccess) return hip_status(e, "hipGraphInstantiate");
-        }
-        for (int i = 0; i < n_steps; ++i) {
-            e = hipGraphLaunch(s->gexec, s->stream);
-            if (e != hipSuccess) return hip_status(e, "hipGraphLaunch");
-        }
+            return le;
+        });
+        if (e != hipSuccess) return hip_status(e, "step graph");
     } else {
         for (int i = 0; i < n_steps; ++i) {
             launch_step(a, s->lists, s->stream, &e);
