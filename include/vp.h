@@ -233,8 +233,10 @@ vp_status vp_plan_tiles(const vp_plan* plan, const vp_options* opts, vp_tiles* o
 
 /* d_out[B][n][n] = M_b . DFT2(P_b V) - (d_y ? M_b . d_y : 0): the forward model
  * of Section 4.2 applied to d_vol[T][S][n][n]. Device scratch of B*n*n complex
- * values (twice that when T > 1) is taken from the stream-ordered allocator
- * and released on the stream. */
+ * values (twice that when T > 1) is a workspace that the plan keeps for the stream (at most
+ * four of at most 64 MiB per device, freed with the plan), else stream-ordered memory released
+ * on the stream: above 64 MiB, on a captured or the per-thread default stream, or with every
+ * kept workspace in use or another stream's. */
 vp_status vp_forward(const vp_plan* plan, const vp_c64* d_vol, const vp_c64* d_y, vp_c64* d_out, void* stream);
 
 /* vp_forward without any allocation, for callers that cannot allocate device memory
@@ -267,8 +269,8 @@ vp_status vp_adjoint(const vp_plan* plan, const vp_c64* d_kres, vp_c64* d_grad, 
  * gridding (Kaiser-Bessel kernel of width 6 on a grid oversampled 2x; about 1e-5 of the
  * definition). Adjoint: d_grad (+)= the exact transpose of the forward (gather form, no
  * atomics). Device pointers on the plan's device, asynchronous on `stream`; scratch of
- * B (2n)^2 complex values plus the blade images comes from the stream-ordered
- * allocator. VP_ERR_UNSUPPORTED if 2n is above the largest transform length (512). */
+ * B (2n)^2 complex values plus the blade images as for vp_forward.
+ * VP_ERR_UNSUPPORTED if 2n is above the largest transform length (512). */
 vp_status vp_nu_forward(const vp_plan* plan, const vp_c64* d_vol, const vp_c64* d_y, vp_c64* d_out, void* stream);
 vp_status vp_nu_adjoint(const vp_plan* plan, const vp_c64* d_samples, vp_c64* d_grad, int32_t accumulate,
                         void* stream);
@@ -396,7 +398,8 @@ vp_status vp_session_set_state(vp_session* session, const vp_c64* volume, const 
  * milliseconds of each stage to stage_ms[5]: projection, forward row DFT,
  * column pass (DFT, mask, residual, inverse DFT), inverse row DFT, and the
  * gather with the regulariser gradient and optimiser update (whose first block
- * also advances the step counter). */
+ * also advances the step counter). For n <= 64 one kernel runs all DFT passes; its time is
+ * the column pass's. */
 vp_status vp_session_stage_times(vp_session* session, int32_t n_steps, double* stage_ms);
 
 vp_status vp_session_destroy(vp_session* session);
