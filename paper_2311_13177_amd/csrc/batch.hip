@@ -43,7 +43,7 @@ static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
         }
         t.proj_rows = proj_rows_for(plans);
         gather_shape_for(voxels, big->plan->S, &t.gath_rows, &t.gath_sc);
-        if (!t.gath_res) t.gath_sc = std::min(t.gath_sc, 16 / t.gath_rows);
+        if (!t.gath_res) t.gath_sc = std::min(t.gath_sc, kPhasedStep / t.gath_rows);
         same = same && t == big->layout->tiles;
     }
     if (same) return t;

@@ -223,7 +223,7 @@ struct DenseStep {
 vp_status dense_setup(const vp_plan* p, DenseStep* ds, const vp_options* o = nullptr) {
     vp_status st = plan_per_blade(p, &ds->q);
     if (st == VP_OK) st = plan_tables(ds->q, &ds->tabs);
-    Tiles t = ds->q->base_tiles;
+    Tiles t = store_tiles(ds->q);
     if (st == VP_OK && !tuned_tiles(ds->q, ds->tabs->device, o ? o->optimizer : VP_OPT_ADAM, &t) && o &&
         o->autotune) {
         vp_options to = *o;

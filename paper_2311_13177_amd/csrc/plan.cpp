@@ -223,6 +223,16 @@ void gather_shape_for(uint64_t voxels, int S, int* rows, int* sc) {
     while (*sc > 1 && (uint64_t)(*rows * *sc) > per_lane) *sc /= 2;
 }
 
+Tiles store_tiles(const vp_plan* p) {
+    Tiles t = p->base_tiles;
+    // (four-wave items: the plan fell back to the smallest shape)
+    if (!t.gath_res && t.gath_w == 8) {
+        gather_shape_for(p->voxels(), p->S, &t.gath_rows, &t.gath_sc);
+        t.gath_sc = std::min(t.gath_sc, 16 / t.gath_rows);
+    }
+    return t;
+}
+
 Tiles heuristic_tiles(const vp_plan* p) {
     // Projection items: eight waves (a part of the knot each), or four where that leaves fewer
     // waves of a knot's last group without a part (12 parts of 256^2 x 32 bins: 20 us in three
@@ -563,7 +573,7 @@ static vp_status plan_create(const vp_geometry* g, bool per_blade, vp_plan** out
             // the knot's parts do not fit at once: stage them a few at a time
             clear_error();
             p->base_tiles.gath_res = 0;
-            p->base_tiles.gath_sc = std::min(p->base_tiles.gath_sc, 16 / p->base_tiles.gath_rows);
+            p->base_tiles.gath_sc = std::min(p->base_tiles.gath_sc, kPhasedStep / p->base_tiles.gath_rows);
             st = plan_layout(p.get(), p->base_tiles, &L);
         }
         if (st != VP_OK) {

@@ -189,6 +189,13 @@ vp_status device_layout(const vp_plan* plan, DeviceTables* tabs, const Layout* L
 int proj_rows_for(const std::vector<const vp_plan*>& plans);
 // Rows and bins per wave of the gather items for one launch over `voxels` voxels.
 void gather_shape_for(uint64_t voxels, int S, int* rows, int* sc);
+// Rows by bins of a wave of the phased gather fused with the update: the update's registers beside
+// sixteen sums leave too few waves (fused 4 x 4 against 4 x 2: 384^2 x 64 bins x 24 blades 227 and 207
+// us, x 8 knots 1062 and 1007 us, a batch of six slices of 128^2 to 256^2 126 and 99 us).
+constexpr int kPhasedStep = 8;
+// The plan's own shape where the gather only stores (operators, K-Planes): up to sixteen sums in
+// the phased one (with the update pass 384^2 x 64 x 8 knots: 4 x 4 1153 us, 4 x 2 1209 us).
+Tiles store_tiles(const vp_plan* plan);
 // Tile shape chosen without measuring, from the plan's sizes.
 Tiles heuristic_tiles(const vp_plan* plan);
 

@@ -398,7 +398,7 @@ extern "C" vp_status vp_plan_destroy(vp_plan* p) {
 namespace {
 
 // Operator calls use the tuned tile shape recorded for the plan's sizes on the current
-// device, else the plan's heuristic shape.
+// device, else the plan's own for a gather that stores.
 struct OpScope {
     const vp_plan* p;
     DeviceTables* t = nullptr;
@@ -411,7 +411,7 @@ struct OpScope {
     vp_status begin(bool need_work) {
         vp_status st = plan_tables(p, &t);
         if (st != VP_OK) return st;
-        Tiles tl = p->base_tiles;
+        Tiles tl = store_tiles(p);
         (void)tuned_tiles(p, t->device, VP_OPT_ADAM, &tl);
         st = plan_layout(p, tl, &lay);
         if (st != VP_OK) st = plan_layout(p, p->base_tiles, &lay);
@@ -507,14 +507,14 @@ vp_status scratch_address(int dev, float2** out) {
 // already: nothing is built, uploaded or allocated here.
 vp_status existing_tables(const vp_plan* p, int dev, const DeviceTables** t, const Layout** lay,
                           const DeviceLayout** dl) {
-    Tiles want = p->base_tiles;
+    Tiles want = store_tiles(p);
     (void)tuned_tiles(p, dev, VP_OPT_ADAM, &want);
     std::lock_guard<std::mutex> lk(p->mu);
     auto it = p->dev.find(dev);
     if (it == p->dev.end())
         return fail(VP_ERR_STATE, "vp_forward_noalloc: the plan has no tables on device %d yet", dev);
     const DeviceTables* tab = it->second.get();
-    for (const Tiles& tl : {want, p->base_tiles}) {
+    for (const Tiles& tl : {want, store_tiles(p), p->base_tiles}) {
         auto hl = p->layouts.find(tl.key());
         auto dlit = tab->layouts.find(tl.key());
         if (hl != p->layouts.end() && dlit != tab->layouts.end()) {
