@@ -538,9 +538,9 @@ __global__ __launch_bounds__(kThreads) void k_cols(const KArgs a) {
 // the last two. Group g of 256 threads does what the passes' items of rows and of columns 16 g ..
 // 16 g + 15 do, in the same order, so the results (loss partials too) are the same bits.
 // For lengths up to kBladeN, where a pass has at most four items per blade and its time is that
-// of a launch and of a trip through memory. Bound by the latency of one block's loads and
-// stores: without the barriers inside a pass and with the twiddles in registers it takes as long. (Five blades of 64^2: 15 us in three launches, 11 us here, and two launches
-// fewer a step.)
+// of a launch and of a trip through memory. Bound by the latency of one block's loads and stores:
+// without the barriers inside a pass and with the twiddles in registers it takes as long. (Five
+// blades of 64^2: 15 us in three launches, 11 us here, and two launches fewer a step.)
 template <int NC>
 __global__ __launch_bounds__(4 * kThreads) void k_blade(const KArgs a) {
     extern __shared__ float2 sm[];
