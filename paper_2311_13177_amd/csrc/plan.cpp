@@ -128,7 +128,8 @@ static vp_status build_layout(const vp_plan* p, const Tiles& t, Layout* L) {
         }
     }
     L->re_proj = 1;
-    int re_even = 1;  // the same regions from even columns, even columns wide
+    // the same regions from even columns, even columns wide (16-byte units)
+    int re_even = 1;
     for (const ProjGroup& gr : L->groups) {
         L->re_proj = std::max(L->re_proj, region(t.proj_rows, gr.ox_min, gr.ox_max, gr.oy_min, gr.oy_max));
         re_even = std::max(re_even, region(t.proj_rows, gr.ox_min & ~1, gr.ox_max | 1, gr.oy_min, gr.oy_max));
@@ -139,7 +140,8 @@ static vp_status build_layout(const vp_plan* p, const Tiles& t, Layout* L) {
     if (L->re_proj > kStageMax * kThreads || L->re_gath > kStageMax * kThreads)
         return fail(VP_ERR_UNSUPPORTED, "tile shape (%d, %d, %d, %d): staged region exceeds the LDS staging",
                     t.proj_rows, t.proj_gw, t.gath_rows, t.gath_sc);
-    L->re_proj = std::max(L->re_proj, re_even);
+    // (above half the limit the launch takes 4-byte units, which stage the exact region)
+    L->re_proj = std::max(L->re_proj, std::min(re_even, kStageMax * kThreads));
     L->lds_res = 0;
     if (t.gath_res) {
         // every part of a knot resident at once: part j of knot kt at [j * region, (j + 1) * region)
