@@ -136,9 +136,9 @@ __global__ __launch_bounds__(64 * NW) void k_project(const KArgs a, int pb) {
 static inline int grid_for(int ntasks) { return ntasks < 1 ? 1 : (ntasks > (1 << 20) ? (1 << 20) : ntasks); }
 
 // Units per thread, planes per phase and phases of the ring (at most 64 KiB) follow the largest
-// region of the launch.
+// region of the launch. narrow: 4-byte units (an odd n, or a volume that is not on 16 bytes).
 template <int GW, int PPT, int NW>
-static void project_variant(const KArgs& a, int re, bool odd, hipStream_t s) {
+static void project_variant(const KArgs& a, int re, bool narrow, hipStream_t s) {
     const dim3 g(grid_for(a.ntasks)), b(64 * NW);
     constexpr int W = 8 / NW;
     // a plane's LDS bytes: whole chunks of a wave's units, at least as many as SE asks for
@@ -149,8 +149,8 @@ static void project_variant(const KArgs& a, int re, bool odd, hipStream_t s) {
         hipLaunchKernelGGL((k_project<GW, PPT, SE, P, D, UB, NW>), g, b, (D) * (P) * pb, s, a, pb); \
     } while (0)
     if (re > 2048) PL(16 * W, 1, 2, 4);
-    else if (odd && re > 1024) PL(8 * W, 1, 3, 4);
-    else if (odd) PL(4 * W, 1, 4, 4);
+    else if (narrow && re > 1024) PL(8 * W, 1, 3, 4);
+    else if (narrow) PL(4 * W, 1, 4, 4);
     else if (re > 1024) PL(2 * W, 1, 3, 16);
     else if (NW == 4 && re <= 512) PL(1, 2, 2, 16);
     else PL(W, 2, 2, 16);
@@ -161,11 +161,13 @@ hipError_t launch_project(const KArgs& a, int rows, int gw, int waves, int re, b
     if (a.ntasks <= 0) return hipSuccess;
     if (!proj_tiles_ok(rows, gw) || !item_waves_ok(waves) || re < 1 || re > kStageMax * kThreads)
         return hipErrorInvalidValue;
+    // a caller's volume is on 8 bytes; a descriptor array's are allocations of the sessions
+    const bool narrow = odd || (!a.descs && (((uintptr_t)a.one.vol[0] | (uintptr_t)a.one.vol[1]) & 15) != 0);
 #define PV(R, G)                                                            \
     case R * 16 + G:                                                        \
         if constexpr (proj_tiles_ok(R, G)) {                                \
-            if (waves == 8) project_variant<G, R, 8>(a, re, odd, s);        \
-            else project_variant<G, R, 4>(a, re, odd, s);                   \
+            if (waves == 8) project_variant<G, R, 8>(a, re, narrow, s);     \
+            else project_variant<G, R, 4>(a, re, narrow, s);                \
         }                                                                   \
         break
     switch (rows * 16 + gw) {
