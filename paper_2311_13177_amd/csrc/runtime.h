@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "plan.h"
@@ -103,12 +104,16 @@ vp_status hip_status(hipError_t e, const char* what);
 vp_status check_options(const vp_plan* p, const vp_options* o);
 
 // The captured steps of a fit: a graph of one step and one of kMany. Between two graphs the GPU
-// idles for 8 us (static 64^2: 26 us of kernels in a step of 34 us), between the kernels of
-// one for none; eight steps a graph leave 1 us a step, and every count of steps is a few
-// graphs. The larger one is captured once a fit asks for 2 kMany steps in all: it costs about
-// what it saves by then.
+// idles for 5 to 8 us (static 64^2: 27 us of kernels in a step of 32 us), between the kernels of one
+// for none; eight steps a graph leave 1 us a step, and every count of steps is a few graphs.
+// Capturing the larger graph takes the host 0.2 ms (64^2) to 0.9 ms (blade-aligned), what it gains
+// in 50 to 200 steps. It is therefore captured behind kLead single steps, which keep the GPU busy
+// meanwhile, by a call of twice as many, or of kMany once a fit in shorter calls has replayed kLong.
+// First call of a new fit, one step a graph / the larger graph captured before the first step /
+// behind the lead, ms: 64^2 x 40 steps 1.47 / 1.38 / 1.41, x 100 3.41 / 3.01 / 3.08, 256^2 x 40 4.06 /
+// 4.14 / 3.88, blade-aligned 256^2 x 40 8.37 / 8.56 / 8.15, K-Planes 192^2 x 40 46.4 / 47.6 / 46.5.
 struct StepGraph {
-    static constexpr int kMany = 8;
+    static constexpr int kMany = 8, kLead = 2 * kMany, kLong = 16 * kMany;
     hipGraph_t graph[2] = {nullptr, nullptr};
     hipGraphExec_t exec[2] = {nullptr, nullptr};
     int64_t replayed = 0;
@@ -127,12 +132,17 @@ struct StepGraph {
     hipError_t run(hipStream_t s, int n, F step) {
         hipError_t e = hipSuccess;
         int left = n;
-        if (left >= kMany && (exec[1] || n + replayed >= 2 * kMany)) {
-            if (!exec[1]) e = capture(s, 1, kMany, step);
-            for (; e == hipSuccess && left >= kMany; left -= kMany) e = hipGraphLaunch(exec[1], s);
+        auto singles = [&](int k) {
+            if (k > 0 && !exec[0]) e = capture(s, 0, 1, step);
+            for (; e == hipSuccess && k > 0; --k, --left) e = hipGraphLaunch(exec[0], s);
+        };
+        if (!exec[1] && (n >= 2 * kLead || (n >= kMany && replayed >= kLong))) {
+            singles(std::min(left, kLead));
+            if (e == hipSuccess) e = capture(s, 1, kMany, step);
         }
-        if (e == hipSuccess && left > 0 && !exec[0]) e = capture(s, 0, 1, step);
-        for (; e == hipSuccess && left > 0; --left) e = hipGraphLaunch(exec[0], s);
+        if (exec[1])
+            for (; e == hipSuccess && left >= kMany; left -= kMany) e = hipGraphLaunch(exec[1], s);
+        if (e == hipSuccess) singles(left);
         replayed += n;
         return e;
     }
