@@ -52,9 +52,10 @@ struct DeviceLayout {
 
 // Workspaces that the operator calls of a plan keep on one device, so that a call pays neither an
 // allocation nor a free (24 us of host time a pair; a 64^2 forward's three launches take 14 us).
-// A slot belongs to one stream and to one call at a time. The call that takes it again
-// first waits, on its stream, for the event of the call before, so a stream made at a destroyed
-// one's address is safe too. A call gets stream-ordered memory of its own instead while its stream
+// A slot belongs to one stream and to one call at a time; a call takes the smallest that
+// fits (blade-aligned calls hold two, of different sizes). The call that takes it again first waits,
+// on its stream, for the event of the call before, so a stream made at a destroyed one's
+// address is safe too. A call gets stream-ordered memory of its own instead while its stream
 // is captured (a graph's workspace may not be shared with later calls), on the per-thread default
 // stream, above kKeepBytes (there the kernels take 300 us and more and the host runs ahead), and
 // where all kSlots belong to others. The slots are freed with the plan.

@@ -42,20 +42,23 @@ hipError_t Workspace::take(WorkspaceSlots* slots, size_t bytes, hipStream_t stre
     }
     if (keep) {
         std::lock_guard<std::mutex> lk(slots->mu);
-        int fresh = -1;
+        int fresh = -1, best = -1;
         for (int i = 0; i < WorkspaceSlots::kSlots; ++i) {
-            WorkspaceSlots::Slot& w = slots->slot[i];
+            const WorkspaceSlots::Slot& w = slots->slot[i];
             if (!w.ptr && !w.busy) fresh = i;
             if (!w.ptr || w.busy || w.stream != s || w.bytes < bytes) continue;
-            if (hipStreamWaitEvent(s, w.done, 0) != hipSuccess) {
-                (void)hipGetLastError();
-                continue;
+            if (best < 0 || w.bytes < slots->slot[best].bytes) best = i;
+        }
+        if (best >= 0) {
+            WorkspaceSlots::Slot& w = slots->slot[best];
+            if (hipStreamWaitEvent(s, w.done, 0) == hipSuccess) {
+                w.busy = true;
+                from = slots;
+                slot = best;
+                ptr = w.ptr;
+                return hipSuccess;
             }
-            w.busy = true;
-            from = slots;
-            slot = i;
-            ptr = w.ptr;
-            return hipSuccess;
+            (void)hipGetLastError();
         }
         if (fresh >= 0) {
             WorkspaceSlots::Slot& w = slots->slot[fresh];
