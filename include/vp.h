@@ -236,7 +236,7 @@ vp_status vp_plan_tiles(const vp_plan* plan, const vp_options* opts, vp_tiles* o
  * values (twice that when T > 1) is a workspace that the plan keeps for the stream (at most
  * four of at most 64 MiB per device, freed with the plan), else stream-ordered memory released
  * on the stream: above 64 MiB, on a captured or the per-thread default stream, or with every
- * kept workspace in use or another stream's. */
+ * kept workspace at work. */
 vp_status vp_forward(const vp_plan* plan, const vp_c64* d_vol, const vp_c64* d_y, vp_c64* d_out, void* stream);
 
 /* vp_forward without any allocation, for callers that cannot allocate device memory

@@ -55,10 +55,12 @@ struct DeviceLayout {
 // A slot belongs to one stream and to one call at a time; a call takes the smallest that
 // fits (blade-aligned calls hold two, of different sizes). The call that takes it again first waits,
 // on its stream, for the event of the call before, so a stream made at a destroyed one's
-// address is safe too. A call gets stream-ordered memory of its own instead while its stream
+// address is safe too. Where a stream has none and no slot is empty, it takes one over that is idle
+// and whose last call is done on the device (streams come and go; at once one that fits, else
+// replaced by one that does). A call gets stream-ordered memory of its own instead while its stream
 // is captured (a graph's workspace may not be shared with later calls), on the per-thread default
 // stream, above kKeepBytes (there the kernels take 300 us and more and the host runs ahead), and
-// where all kSlots belong to others. The slots are freed with the plan.
+// where all kSlots are at work. The slots are freed with the plan.
 struct WorkspaceSlots {
     static constexpr int kSlots = 4;
     static constexpr size_t kKeepBytes = (size_t)64 << 20;
@@ -68,9 +70,12 @@ struct WorkspaceSlots {
         hipStream_t stream = nullptr;
         hipEvent_t done = nullptr;
         bool busy = false;
+        uint64_t used = 0;  // the call that took it last
     };
     std::mutex mu;
     Slot slot[kSlots];
+    uint64_t calls = 0;
+    int claim(size_t bytes, hipStream_t s);
     ~WorkspaceSlots();
 };
 // One call's workspace: a slot, or stream-ordered memory.

@@ -32,6 +32,67 @@ WorkspaceSlots::~WorkspaceSlots() {
     }
 }
 
+// Whether the work that the event was last recorded behind is done. (A query is not allowed while
+// any thread captures in the strict mode, and must not break that capture.)
+static bool event_done(hipEvent_t ev) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const bool done = hipEventQuery(ev) == hipSuccess;
+    if (!done) (void)hipGetLastError();
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return done;
+}
+
+// A slot for `bytes` on stream s, marked busy: one of the stream's, else an empty one, else one
+// that is idle and finished. Memory comes with it unless ptr is null. -1: none.
+int WorkspaceSlots::claim(size_t bytes, hipStream_t s) {
+    int own = -1, empty = -1, spare = -1;
+    for (int i = 0; i < kSlots; ++i) {
+        const Slot& w = slot[i];
+        if (w.busy) continue;
+        if (!w.ptr) empty = i;
+        else if (w.stream == s && w.bytes >= bytes && (own < 0 || w.bytes < slot[own].bytes)) own = i;
+    }
+    if (own >= 0) {
+        if (hipStreamWaitEvent(s, slot[own].done, 0) == hipSuccess) {
+            slot[own].busy = true;
+            return own;
+        }
+        (void)hipGetLastError();
+    }
+    if (empty >= 0) {
+        Slot& w = slot[empty];
+        if (hipEventCreateWithFlags(&w.done, hipEventDisableTiming) == hipSuccess) {
+            w.stream = s;
+            w.busy = true;
+            return empty;
+        }
+        (void)hipGetLastError();
+        return -1;
+    }
+    for (int i = 0; i < kSlots; ++i) {
+        const Slot& w = slot[i];
+        if (w.busy || !w.ptr || !event_done(w.done)) continue;
+        // one that fits before one that does not, then the one longest unused
+        const bool fits = w.bytes >= bytes;
+        if (spare < 0 || fits > (slot[spare].bytes >= bytes) ||
+            (fits == (slot[spare].bytes >= bytes) && w.used < slot[spare].used))
+            spare = i;
+    }
+    if (spare < 0) return -1;
+    Slot& w = slot[spare];
+    if (w.bytes < bytes) {
+        (void)hipFreeAsync(w.ptr, s);
+        w.ptr = nullptr;
+    }
+    w.stream = s;
+    w.busy = true;
+    return spare;
+}
+
 hipError_t Workspace::take(WorkspaceSlots* slots, size_t bytes, hipStream_t stream) {
     s = stream;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -42,41 +103,23 @@ hipError_t Workspace::take(WorkspaceSlots* slots, size_t bytes, hipStream_t stre
     }
     if (keep) {
         std::lock_guard<std::mutex> lk(slots->mu);
-        int fresh = -1, best = -1;
-        for (int i = 0; i < WorkspaceSlots::kSlots; ++i) {
-            const WorkspaceSlots::Slot& w = slots->slot[i];
-            if (!w.ptr && !w.busy) fresh = i;
-            if (!w.ptr || w.busy || w.stream != s || w.bytes < bytes) continue;
-            if (best < 0 || w.bytes < slots->slot[best].bytes) best = i;
-        }
-        if (best >= 0) {
-            WorkspaceSlots::Slot& w = slots->slot[best];
-            if (hipStreamWaitEvent(s, w.done, 0) == hipSuccess) {
-                w.busy = true;
-                from = slots;
-                slot = best;
-                ptr = w.ptr;
-                return hipSuccess;
-            }
-            (void)hipGetLastError();
-        }
-        if (fresh >= 0) {
-            WorkspaceSlots::Slot& w = slots->slot[fresh];
-            if (hipEventCreateWithFlags(&w.done, hipEventDisableTiming) == hipSuccess) {
-                const hipError_t e = hipMallocAsync(&ptr, bytes, s);
+        const int i = slots->claim(bytes, s);
+        if (i >= 0) {
+            WorkspaceSlots::Slot& w = slots->slot[i];
+            if (!w.ptr) {
+                const hipError_t e = hipMallocAsync(&w.ptr, bytes, s);
                 if (e != hipSuccess) {
                     (void)hipEventDestroy(w.done);
+                    w = WorkspaceSlots::Slot{};
                     return e;
                 }
-                w.ptr = ptr;
                 w.bytes = bytes;
-                w.stream = s;
-                w.busy = true;
-                from = slots;
-                slot = fresh;
-                return hipSuccess;
             }
-            (void)hipGetLastError();
+            w.used = ++slots->calls;
+            from = slots;
+            slot = i;
+            ptr = w.ptr;
+            return hipSuccess;
         }
     }
     return hipMallocAsync(&ptr, bytes, s);

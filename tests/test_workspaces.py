@@ -8,7 +8,7 @@ from host_build import run_host
 from paper_2311_13177_amd import binding
 
 
-@pytest.mark.parametrize("what", ["sizes", "own"])
+@pytest.mark.parametrize("what", ["sizes", "own", "streams"])
 def test_kept_workspaces(tmp_path, what):
     binding.lib()
     rc, out = run_host(tmp_path, "workspaces", what)
