@@ -25,7 +25,8 @@ SliceGroup::~SliceGroup() {
 // One tile shape for a whole group (the kernels take it as template parameters): the
 // shape every session already uses if they agree, else the largest slice's shape when it
 // fits every slice, else that shape with two-row tiles, which always fits. Where that shape
-// is the plan's own choice, its rows and bins per wave follow the work of the whole group.
+// is the plan's own choice (not asked for, not tuned), its rows and bins per wave follow the work
+// of the whole group.
 static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
     const vp_session* big = sessions[0];
     bool same = true;
@@ -34,16 +35,10 @@ static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
         if (s->plan->voxels() > big->plan->voxels()) big = s;
     }
     Tiles t = big->layout->tiles;
-    if (t == big->plan->base_tiles && sessions.size() > 1) {
+    if (big->own_shape && sessions.size() > 1) {
         std::vector<const vp_plan*> plans;
-        uint64_t voxels = 0;
-        for (const vp_session* s : sessions) {
-            plans.push_back(s->plan);
-            voxels += s->plan->voxels();
-        }
-        t.proj_rows = proj_rows_for(plans);
-        gather_shape_for(voxels, big->plan->S, &t.gath_rows, &t.gath_sc);
-        if (!t.gath_res) t.gath_sc = std::min(t.gath_sc, kPhasedStep / t.gath_rows);
+        for (const vp_session* s : sessions) plans.push_back(s->plan);
+        t = group_shape(t, plans, big->plan->S);
         same = same && t == big->layout->tiles;
     }
     if (same) return t;

@@ -225,13 +225,23 @@ void gather_shape_for(uint64_t voxels, int S, int* rows, int* sc) {
     while (*sc > 1 && (uint64_t)(*rows * *sc) > per_lane) *sc /= 2;
 }
 
+// (Four-wave gather items: the plan fell back to the smallest shape, which stays.)
 Tiles store_tiles(const vp_plan* p) {
     Tiles t = p->base_tiles;
-    // (four-wave items: the plan fell back to the smallest shape)
     if (!t.gath_res && t.gath_w == 8) {
         gather_shape_for(p->voxels(), p->S, &t.gath_rows, &t.gath_sc);
         t.gath_sc = std::min(t.gath_sc, 16 / t.gath_rows);
     }
+    return t;
+}
+
+Tiles group_shape(Tiles t, const std::vector<const vp_plan*>& plans, int S) {
+    if (t.gath_w != 8) return t;
+    uint64_t voxels = 0;
+    for (const vp_plan* p : plans) voxels += p->voxels();
+    t.proj_rows = proj_rows_for(plans);
+    gather_shape_for(voxels, S, &t.gath_rows, &t.gath_sc);
+    if (!t.gath_res) t.gath_sc = std::min(t.gath_sc, kPhasedStep / t.gath_rows);
     return t;
 }
 

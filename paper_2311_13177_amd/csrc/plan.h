@@ -202,6 +202,8 @@ constexpr int kPhasedStep = 8;
 // The plan's own shape where the gather only stores (operators, K-Planes): up to sixteen sums in
 // the phased one (with the update pass 384^2 x 64 x 8 knots: 4 x 4 1153 us, 4 x 2 1209 us).
 Tiles store_tiles(const vp_plan* plan);
+// A plan's own shape t for one step's launches over all of these plans (S: bins of the largest).
+Tiles group_shape(Tiles t, const std::vector<const vp_plan*>& plans, int S);
 // Tile shape chosen without measuring, from the plan's sizes.
 Tiles heuristic_tiles(const vp_plan* plan);
 

@@ -83,8 +83,8 @@ inline int stream_for(uint64_t voxels, int optimizer) {
 hipError_t launch_gather_lists(const KArgs& a, int mode, const StageLists& L, hipStream_t s);
 // Tile shape for a plan under options: explicit tiles from the options, else the tuned
 // shape recorded for this plan's sizes on the device (tuning first when the options ask
-// for it and none is recorded), else the plan's heuristic shape.
-vp_status tiles_for(const vp_plan* p, const vp_options* o, Tiles* out);
+// for it and none is recorded), else the plan's heuristic shape (*own: whether that one).
+vp_status tiles_for(const vp_plan* p, const vp_options* o, Tiles* out, bool* own = nullptr);
 // Tuned shape recorded for the plan's sizes on `device`, if any.
 bool tuned_tiles(const vp_plan* p, int device, int optimizer, Tiles* out);
 // Measures the candidate tile shapes on the current device and records the fastest.
@@ -175,6 +175,7 @@ struct vp_session {
     vp::DeviceTables* tabs = nullptr;
     const vp::Layout* layout = nullptr;
     const vp::DeviceLayout* dlayout = nullptr;
+    bool own_shape = false;  // the layout's shape is the plan's own: neither asked for nor tuned
     float2* vol[2] = {nullptr, nullptr};
     float2* m = nullptr;
     float2* v = nullptr;

@@ -1200,7 +1200,7 @@ vp_status session_alloc(const vp_plan* p, const vp_options* o, const vp_c64* ksp
     st = plan_tables(p, &s->tabs);
     if (st != VP_OK) return st;
     Tiles tl;
-    st = tiles_for(p, o, &tl);
+    st = tiles_for(p, o, &tl, &s->own_shape);
     if (st == VP_OK) st = plan_layout(p, tl, &s->layout);
     if (st == VP_OK) st = device_layout(p, s->tabs, s->layout, &s->dlayout);
     if (st != VP_OK) return st;

@@ -77,7 +77,8 @@ bool tuned_tiles(const vp_plan* p, int device, int optimizer, Tiles* out) {
     return true;
 }
 
-vp_status tiles_for(const vp_plan* p, const vp_options* o, Tiles* out) {
+vp_status tiles_for(const vp_plan* p, const vp_options* o, Tiles* out, bool* own) {
+    if (own) *own = false;
     const vp_tiles& t = o->tiles;
     if (t.proj_rows || t.proj_parts || t.gath_rows || t.gath_bins || t.upd_bins || t.gath_waves || t.proj_waves ||
         t.gath_resident) {
@@ -87,6 +88,7 @@ vp_status tiles_for(const vp_plan* p, const vp_options* o, Tiles* out) {
     }
     if (tuned_tiles(p, o->device, o->optimizer, out)) return VP_OK;
     if (o->autotune) return tune_plan(p, o, out);
+    if (own) *own = true;
     *out = p->base_tiles;
     return VP_OK;
 }
