@@ -200,18 +200,41 @@ static int pow2_ceil(int v) {
     return r;
 }
 
-// The tallest projection tile that still makes twelve waves with a part per CU over the plans
-// of one launch: a taller tile stages less halo per row (192^2 x 16 knots: 8 rows 48 us, 4 rows
-// 57; the tuner also tries 12 rows, 43 us), fewer waves leave CUs idle (256^2, one knot of 12
-// parts: 4 rows 20 us, 8 rows 23).
-int proj_rows_for(const std::vector<const vp_plan*>& plans) {
-    for (int rows : {8, 4, 2}) {
-        uint64_t waves = 0;
-        for (const vp_plan* p : plans)
-            waves += (uint64_t)p->knot_ent.size() * ceil_div(p->n, rows) * ceil_div(p->n, kTileW);
-        if (waves >= 12 * 256) return rows;
+// Projection items of one launch over these plans, per CU.
+static double proj_items(const std::vector<const vp_plan*>& plans, int rows, int group) {
+    uint64_t items = 0;
+    for (const vp_plan* p : plans)
+        for (int kt = 0; kt < p->T; ++kt)
+            items += (uint64_t)ceil_div(p->knot_ptr[kt + 1] - p->knot_ptr[kt], group) * ceil_div(p->n, rows) *
+                     ceil_div(p->n, kTileW);
+    return (double)items / 256.0;
+}
+
+// Rows, parts per wave and waves of the projection items of one launch over these plans. A taller
+// tile stages less halo per row, and a larger group stages each region for more parts; too
+// few items leave CUs idle. Knots of more than eight parts take two parts a wave where eight-row
+// items of sixteen parts still make 1.6 rounds of the CUs (six slices of 256^2 x 32 bins x 12 parts:
+// 58 us, 75 us in groups of four). Else four waves for up to three parts, or where eight leave more
+// waves of the last group without one (256^2 x 32, 12 parts: 20 us in three groups of four, 21 us in
+// eight and four), else eight; eight, four or two rows from 1.6, 1.1 and 0.6 items per CU on (150^2 x 64
+// bins x 4 knots of 4 and 5 parts: 4 rows 35 us, 2 rows 54 us; 300^2 x 64, 4 parts: 2 rows 34 us, 1 row
+// 57 us; 256^2 x 32, 12 parts: 4 rows 22 us, 8 rows 25 us). Over 1100 launches of 1 to 16 slices of
+// 48^2 to 384^2 that is 4 % from the best of the compiled shapes.
+void proj_shape_for(const std::vector<const vp_plan*>& plans, Tiles* t) {
+    int np = 1;
+    for (const vp_plan* p : plans) np = std::max(np, p->max_knot_parts);
+    t->proj_w = np <= 3 || (np > 8 && ceil_div(np, 4) * 4 < ceil_div(np, 8) * 8) ? 4 : 8;
+    t->proj_gw = 1;
+    if (np > 8 && proj_items(plans, 8, 16) >= 1.6) {
+        t->proj_rows = 8;
+        t->proj_gw = 2;
+        t->proj_w = 8;
+        return;
     }
-    return 1;
+    t->proj_rows = proj_items(plans, 8, t->proj_w) >= 1.6   ? 8
+                   : proj_items(plans, 4, t->proj_w) >= 1.1 ? 4
+                   : proj_items(plans, 2, t->proj_w) >= 0.6 ? 2
+                                                            : 1;
 }
 
 // Rows and bins per wave of the gather for one launch over this many voxels: up to 4 rows by
@@ -239,23 +262,17 @@ Tiles group_shape(Tiles t, const std::vector<const vp_plan*>& plans, int S) {
     if (t.gath_w != 8) return t;
     uint64_t voxels = 0;
     for (const vp_plan* p : plans) voxels += p->voxels();
-    t.proj_rows = proj_rows_for(plans);
+    proj_shape_for(plans, &t);
     gather_shape_for(voxels, S, &t.gath_rows, &t.gath_sc);
     if (!t.gath_res) t.gath_sc = std::min(t.gath_sc, kPhasedStep / t.gath_rows);
     return t;
 }
 
 Tiles heuristic_tiles(const vp_plan* p) {
-    // Projection items: eight waves (a part of the knot each), or four where that leaves fewer
-    // waves of a knot's last group without a part (12 parts of 256^2 x 32 bins: 20 us in three
-    // groups of four, 21 us in eight and four; 34 us with two parts per wave in one group).
     // Gather items have every part of the knot resident in LDS (the plan falls back to parts
     // staged a few at a time where they do not fit).
     Tiles t;
-    const int np = std::max(1, p->max_knot_parts);
-    t.proj_w = np <= 4 || (np > 8 && ceil_div(np, 4) * 4 < ceil_div(np, 8) * 8) ? 4 : 8;
-    t.proj_gw = 1;
-    t.proj_rows = proj_rows_for({p});
+    proj_shape_for({p}, &t);
     t.gath_w = 8;
     gather_shape_for(p->voxels(), p->S, &t.gath_rows, &t.gath_sc);
     t.gath_res = 1;

@@ -191,8 +191,8 @@ vp_status plan_tables(const vp_plan* plan, DeviceTables** out);
 vp_status plan_layout(const vp_plan* plan, const Tiles& t, const Layout** out);
 // A layout's tables on the device of `tabs`, uploaded on first use.
 vp_status device_layout(const vp_plan* plan, DeviceTables* tabs, const Layout* L, const DeviceLayout** out);
-// Rows of the projection tiles for one launch over these plans.
-int proj_rows_for(const std::vector<const vp_plan*>& plans);
+// Rows, parts per wave and waves of the projection items for one launch over these plans.
+void proj_shape_for(const std::vector<const vp_plan*>& plans, Tiles* t);
 // Rows and bins per wave of the gather items for one launch over `voxels` voxels.
 void gather_shape_for(uint64_t voxels, int S, int* rows, int* sc);
 // Rows by bins of a wave of the phased gather fused with the update: the update's registers beside
