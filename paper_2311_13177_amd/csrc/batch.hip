@@ -22,11 +22,22 @@ SliceGroup::~SliceGroup() {
     if (d_tasks) (void)hipFree(d_tasks);
 }
 
+static bool fits_all(const std::vector<vp_session*>& sessions, const Tiles& t) {
+    for (const vp_session* s : sessions) {
+        const Layout* L = nullptr;
+        if (plan_layout(s->plan, t, &L) == VP_OK) continue;
+        clear_error();
+        return false;
+    }
+    return true;
+}
+
 // One tile shape for a whole group (the kernels take it as template parameters): the
 // shape every session already uses if they agree, else the largest slice's shape when it
 // fits every slice, else that shape with two-row tiles, which always fits. Where that shape
-// is the plan's own choice (not asked for, not tuned), its rows and bins per wave follow the work
-// of the whole group.
+// is the plan's own choice (not asked for, not tuned), it follows the work of the whole group, with
+// the phased gather where the resident one's larger tiles do not fit (six slices of 96^2 x 16 bins x
+// 16 parts: resident 2 x 1 45 us, phased 4 x 2 35 us).
 static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
     const vp_session* big = sessions[0];
     bool same = true;
@@ -39,19 +50,16 @@ static Tiles group_tiles(const std::vector<vp_session*>& sessions) {
         std::vector<const vp_plan*> plans;
         for (const vp_session* s : sessions) plans.push_back(s->plan);
         t = group_shape(t, plans, big->plan->S);
+        if (t.gath_res && !fits_all(sessions, t)) {
+            t.gath_res = 0;
+            t = group_shape(t, plans, big->plan->S);
+        }
         same = same && t == big->layout->tiles;
     }
-    if (same) return t;
-    for (const vp_session* s : sessions) {
-        const Layout* L = nullptr;
-        if (plan_layout(s->plan, t, &L) != VP_OK) {
-            clear_error();
-            t.proj_rows = 2;
-            t.gath_rows = 2;
-            t.gath_res = 0;
-            break;
-        }
-    }
+    if (same || fits_all(sessions, t)) return t;
+    t.proj_rows = 2;
+    t.gath_rows = 2;
+    t.gath_res = 0;
     return t;
 }
 

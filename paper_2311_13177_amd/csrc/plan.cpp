@@ -237,46 +237,59 @@ void proj_shape_for(const std::vector<const vp_plan*>& plans, Tiles* t) {
                                                             : 1;
 }
 
-// Rows and bins per wave of the gather for one launch over this many voxels: up to 4 rows by
-// the bins that cover S with eight waves, less where that leaves fewer than sixteen waves per
-// CU (256^2 x 32 bins: 4 x 4 50 us, 4 x 2 37 us, 4 x 1 44 us; 64^2 x 16: 4 x 2 19 us, 4 x 1 15 us,
-// 2 x 1 13 us).
-void gather_shape_for(uint64_t voxels, int S, int* rows, int* sc) {
-    const uint64_t per_lane = voxels / (64 * 16 * 256);  // voxels a lane may take
-    *rows = per_lane >= 4 ? 4 : 2;
-    *sc = std::min(8, pow2_ceil(ceil_div(S, 8)));
-    while (*sc > 1 && (uint64_t)(*rows * *sc) > per_lane) *sc /= 2;
+// Eight-wave gather items of one launch over these plans, per CU.
+static double gath_items(const std::vector<const vp_plan*>& plans, int rows, int sc) {
+    uint64_t items = 0;
+    for (const vp_plan* p : plans)
+        items += (uint64_t)p->T * ceil_div(p->n, rows) * ceil_div(p->n, kTileW) * ceil_div(p->S, 8 * sc);
+    return (double)items / 256.0;
+}
+
+// Rows and bins per wave of the gather items of one launch over these plans, for up to `sums` sums
+// a lane: the largest that leave enough items per CU, and no more bins than cover S with eight
+// waves. Four rows by eight, four, two and one bin above 3, 1.5, 1 and 0.5 items per CU, else two
+// by one. (Resident: 256^2 x 64 bins x 12 parts, 2 items, 4 x 4 51 us, 4 x 2 57 us; 256^2 x 32 x 8, 1 item,
+// 33 and 28 us; 192^2 x 32 x 8, 1.1 items, 4 x 2 27 us, 4 x 1 29 us; 64^2 x 64 x 4 knots, 1 item, 22 and 21 us;
+// 128^2 x 16 x 3 parts, 0.5 items, 4 x 1 13 us, 2 x 1 12 us. Phased: 300^2 x 4 x 8, 1.5 items, 4 x 1 18 us, 2 x 1
+// 24 us; 256^2 x 32 x 12, 2 items, 4 x 2 34 us, 4 x 1 44 us.) Over 1100 launches of 1 to 16 slices of 48^2 to
+// 384^2 that is 2 % from the best of the compiled shapes.
+static void gather_shape_for(const std::vector<const vp_plan*>& plans, int S, int sums, Tiles* t) {
+    struct Line {
+        int sc;
+        double items;
+    };
+    const int cap = pow2_ceil(ceil_div(S, 8));
+    for (const Line& l : {Line{8, 3.0}, Line{4, 1.5}, Line{2, 1.0}, Line{1, 0.5}}) {
+        if (l.sc > cap || 4 * l.sc > sums || gath_items(plans, 4, l.sc) <= l.items) continue;
+        t->gath_rows = 4;
+        t->gath_sc = l.sc;
+        return;
+    }
+    t->gath_rows = 2;
+    t->gath_sc = 1;
 }
 
 // (Four-wave gather items: the plan fell back to the smallest shape, which stays.)
 Tiles store_tiles(const vp_plan* p) {
     Tiles t = p->base_tiles;
-    if (!t.gath_res && t.gath_w == 8) {
-        gather_shape_for(p->voxels(), p->S, &t.gath_rows, &t.gath_sc);
-        t.gath_sc = std::min(t.gath_sc, 16 / t.gath_rows);
-    }
+    if (!t.gath_res && t.gath_w == 8) gather_shape_for({p}, p->S, kPhasedStore, &t);
     return t;
 }
 
 Tiles group_shape(Tiles t, const std::vector<const vp_plan*>& plans, int S) {
     if (t.gath_w != 8) return t;
-    uint64_t voxels = 0;
-    for (const vp_plan* p : plans) voxels += p->voxels();
     proj_shape_for(plans, &t);
-    gather_shape_for(voxels, S, &t.gath_rows, &t.gath_sc);
-    if (!t.gath_res) t.gath_sc = std::min(t.gath_sc, kPhasedStep / t.gath_rows);
+    gather_shape_for(plans, S, t.gath_res ? kResidentSums : kPhasedStep, &t);
     return t;
 }
 
-Tiles heuristic_tiles(const vp_plan* p) {
-    // Gather items have every part of the knot resident in LDS (the plan falls back to parts
-    // staged a few at a time where they do not fit).
+// Gather items have every part of the knot resident in LDS (the plan falls back to parts
+// staged a few at a time where they do not fit).
+Tiles heuristic_tiles(const vp_plan* p, bool resident) {
     Tiles t;
-    proj_shape_for({p}, &t);
     t.gath_w = 8;
-    gather_shape_for(p->voxels(), p->S, &t.gath_rows, &t.gath_sc);
-    t.gath_res = 1;
-    return t;
+    t.gath_res = resident;
+    return group_shape(t, {p}, p->S);
 }
 
 vp_status plan_layout(const vp_plan* p, const Tiles& t, const Layout** out) {
@@ -595,14 +608,13 @@ static vp_status plan_create(const vp_geometry* g, bool per_blade, vp_plan** out
         const int npb = ceil_div(n * n, kVoxItem);
         for (int kt = 0; kt < T; ++kt)
             for (int pb = 0; pb < npb; ++pb) p->t_render.push_back(Task{0, kt, pb, 0});
-        p->base_tiles = heuristic_tiles(p.get());
+        p->base_tiles = heuristic_tiles(p.get(), true);
         const Layout* L = nullptr;
         vp_status st = plan_layout(p.get(), p->base_tiles, &L);
         if (st != VP_OK) {
             // the knot's parts do not fit at once: stage them a few at a time
             clear_error();
-            p->base_tiles.gath_res = 0;
-            p->base_tiles.gath_sc = std::min(p->base_tiles.gath_sc, kPhasedStep / p->base_tiles.gath_rows);
+            p->base_tiles = heuristic_tiles(p.get(), false);
             st = plan_layout(p.get(), p->base_tiles, &L);
         }
         if (st != VP_OK) {

@@ -193,19 +193,17 @@ vp_status plan_layout(const vp_plan* plan, const Tiles& t, const Layout** out);
 vp_status device_layout(const vp_plan* plan, DeviceTables* tabs, const Layout* L, const DeviceLayout** out);
 // Rows, parts per wave and waves of the projection items for one launch over these plans.
 void proj_shape_for(const std::vector<const vp_plan*>& plans, Tiles* t);
-// Rows and bins per wave of the gather items for one launch over `voxels` voxels.
-void gather_shape_for(uint64_t voxels, int S, int* rows, int* sc);
-// Rows by bins of a wave of the phased gather fused with the update: the update's registers beside
-// sixteen sums leave too few waves (fused 4 x 4 against 4 x 2: 384^2 x 64 bins x 24 blades 227 and 207
-// us, x 8 knots 1062 and 1007 us, a batch of six slices of 128^2 to 256^2 126 and 99 us).
-constexpr int kPhasedStep = 8;
-// The plan's own shape where the gather only stores (operators, K-Planes): up to sixteen sums in
-// the phased one (with the update pass 384^2 x 64 x 8 knots: 4 x 4 1153 us, 4 x 2 1209 us).
+// Rows by bins of a wave of the gather: the resident one keeps a bin's sums at a time; the phased
+// one all of them, beside the update's registers where it is fused (384^2 x 64 bins x 24 blades: 4 x 4
+// 227 us, 4 x 2 207 us, x 8 knots 1062 and 1007 us) and alone where it stores (384^2 x 64 x 8 knots with
+// the update pass: 4 x 4 1153 us, 4 x 2 1209 us).
+constexpr int kResidentSums = 32, kPhasedStore = 16, kPhasedStep = 8;
+// The plan's own shape where the gather only stores (operators, K-Planes).
 Tiles store_tiles(const vp_plan* plan);
 // A plan's own shape t for one step's launches over all of these plans (S: bins of the largest).
 Tiles group_shape(Tiles t, const std::vector<const vp_plan*>& plans, int S);
-// Tile shape chosen without measuring, from the plan's sizes.
-Tiles heuristic_tiles(const vp_plan* plan);
+// Tile shape chosen without measuring, from the plan's sizes, with the resident or the phased gather.
+Tiles heuristic_tiles(const vp_plan* plan, bool resident);
 
 // Fills the plan-constant part of a slice descriptor from device tables and a layout.
 void fill_desc(const vp_plan* plan, const DeviceTables* t, const Layout* L, const DeviceLayout* dl, SliceDesc* d);

@@ -30,3 +30,19 @@ def _plan(n, S, T, nb, f):
 def test_projection_shapes(case, best):
     pr, gw, _, _, _, _, pw, _ = _plan(*case).tiles()
     assert (pr, gw, pw) in best
+
+
+# (rows, bins per wave, resident) of the gather with the update
+@pytest.mark.parametrize("case,best", [
+    ((300, 4, 1, 8, 7.2), {(4, 1, 0)}),                # 18 us, 24 with two rows
+    ((300, 4, 1, 24, 2.0), {(4, 1, 0)}),               # 29 us, 38
+    ((225, 16, 1, 8, 6.0), {(4, 1, 0), (4, 2, 0)}),    # 22 and 23 us, 30 with two rows
+    ((300, 16, 1, 24, 7.2), {(4, 2, 0)}),              # 46 us, 58 with one bin
+    ((128, 4, 8, 16, 2.5), {(4, 1, 0), (4, 1, 1)}),    # 14 and 15 us, 18 with two rows
+    ((256, 32, 1, 12, 4.0), {(4, 2, 0)}),
+    ((192, 32, 16, 32, 3.0), {(4, 4, 1)}),
+    ((64, 16, 1, 5, 2.0), {(2, 1, 0), (2, 1, 1)}),
+])
+def test_gather_shapes(case, best):
+    _, _, gr, gb, _, _, _, res = _plan(*case).tiles()
+    assert (gr, gb, res) in best
