@@ -212,28 +212,29 @@ static double proj_items(const std::vector<const vp_plan*>& plans, int rows, int
 
 // Rows, parts per wave and waves of the projection items of one launch over these plans. A taller
 // tile stages less halo per row, and a larger group stages each region for more parts; too
-// few items leave CUs idle. Knots of more than eight parts take two parts a wave where eight-row
-// items of sixteen parts still make 1.6 rounds of the CUs (six slices of 256^2 x 32 bins x 12 parts:
-// 58 us, 75 us in groups of four). Else four waves for up to three parts, or where eight leave more
+// few items leave CUs idle. Knots of more than eight parts take two parts a wave where sixteen to
+// an item leave less than half an item idle and eight-row items still make 1.6 rounds of the CUs
+// (six slices of 256^2 x 32 bins x 12 parts: 58 us, 75 us in groups of four; 384^2 x 64 x 24 parts:
+// 134 us, 101 us in groups of eight). Else four waves for up to four parts, or where eight leave more
 // waves of the last group without one (256^2 x 32, 12 parts: 20 us in three groups of four, 21 us in
-// eight and four), else eight; eight, four or two rows from 1.6, 1.1 and 0.6 items per CU on (150^2 x 64
-// bins x 4 knots of 4 and 5 parts: 4 rows 35 us, 2 rows 54 us; 300^2 x 64, 4 parts: 2 rows 34 us, 1 row
-// 57 us; 256^2 x 32, 12 parts: 4 rows 22 us, 8 rows 25 us). Over 1100 launches of 1 to 16 slices of
-// 48^2 to 384^2 that is 4 % from the best of the compiled shapes.
+// eight and four), else eight; eight, four or two rows from 1.75, 1.5 and 1.2 items per CU on (150^2 x
+// 64 bins x 4 knots of 4 and 5 parts: 4 rows 35 us, 2 rows 54 us; 150^2 x 64 x 8 parts: 1 row 28 us, 2 rows
+// 34 us; 300^2 x 64, 4 parts: 2 rows 34 us, 1 row 57 us; 256^2 x 32, 12 parts: 4 rows 22 us, 8 rows 25 us).
+// Over 1250 launches of 1 to 16 slices of 48^2 to 384^2 that is 4 % from the best of the compiled shapes.
 void proj_shape_for(const std::vector<const vp_plan*>& plans, Tiles* t) {
     int np = 1;
     for (const vp_plan* p : plans) np = std::max(np, p->max_knot_parts);
-    t->proj_w = np <= 3 || (np > 8 && ceil_div(np, 4) * 4 < ceil_div(np, 8) * 8) ? 4 : 8;
-    t->proj_gw = 1;
-    if (np > 8 && proj_items(plans, 8, 16) >= 1.6) {
+    if (np > 8 && ceil_div(np, 16) * 16 - np < 8 && proj_items(plans, 8, 16) >= 1.6) {
         t->proj_rows = 8;
         t->proj_gw = 2;
         t->proj_w = 8;
         return;
     }
-    t->proj_rows = proj_items(plans, 8, t->proj_w) >= 1.6   ? 8
-                   : proj_items(plans, 4, t->proj_w) >= 1.1 ? 4
-                   : proj_items(plans, 2, t->proj_w) >= 0.6 ? 2
+    t->proj_w = np <= 4 || (np > 8 && ceil_div(np, 4) * 4 < ceil_div(np, 8) * 8) ? 4 : 8;
+    t->proj_gw = 1;
+    t->proj_rows = proj_items(plans, 8, t->proj_w) >= 1.75  ? 8
+                   : proj_items(plans, 4, t->proj_w) >= 1.5 ? 4
+                   : proj_items(plans, 2, t->proj_w) >= 1.2 ? 2
                                                             : 1;
 }
 

@@ -26,6 +26,8 @@ def _plan(n, S, T, nb, f):
     ((64, 32, 16, 32, 2.0), {(2, 1, 4), (2, 1, 8), (4, 1, 8), (4, 1, 4)}),  # 18 us, 27 with one row
     ((192, 32, 16, 32, 3.0), {(8, 1, 8)}),
     ((64, 16, 1, 5, 2.0), {(1, 1, 8), (2, 1, 8), (1, 1, 4)}),
+    ((384, 64, 1, 24, 6.5), {(8, 1, 8)}),              # 101 us, 134 in groups of sixteen
+    ((150, 64, 1, 8, 4.8), {(1, 1, 8)}),               # 28 us, 34 with two rows
 ])
 def test_projection_shapes(case, best):
     pr, gw, _, _, _, _, pw, _ = _plan(*case).tiles()
