@@ -63,18 +63,20 @@ __global__ __launch_bounds__(kThreads) void k_baseline_avg(const uint8_t* __rest
         out[(size_t)blockIdx.y * nn + px + v] = cscale(acc[v], 1.0f / ((float)max(c[v], 1) * (float)n));
 }
 
-// Square root of x >= 0 in FP64: the hardware's FP32 reciprocal square root (about 1 ulp), then a
-// Newton step (1e-14 relative) and a correction by the exact residual in FP64, which
-// leaves all but one value in 30000 correctly rounded, with half the library root's instructions
-// (they bound k_psnr: one CU works on an image).
+// Square root of x >= 0 in FP64: the hardware's FP32 reciprocal square root (about 1 ulp), a Newton
+// step of the root and of its reciprocal (2^-46 relative), then a correction by the exact residual in
+// FP64. What is rounded at the end is off by 2^-39 of an ulp: none of six million magnitudes differs
+// from the correctly rounded one (one in a million does with the unrefined reciprocal in the
+// correction). About half the library root's instructions, which bound k_psnr: one CU works on an
+// image (32 frames' baselines and 16 frames' PSNR of 192^2: 47.3 us, 49.6 us with the library's root).
 // Values outside FP32's normal range take the library's.
 __device__ __forceinline__ double sqrt64(double x) {
     if (x == 0.0) return 0.0;
     const float xf = (float)x;
     if (!(xf >= 1.1754944e-38f && xf <= 3.4028235e38f)) return sqrt(x);
     const double y = (double)__builtin_amdgcn_rsqf(xf);
-    const double h = 0.5 * y, g = x * y;
-    const double s = fma(g, fma(-h, g, 0.5), g);
+    const double h0 = 0.5 * y, g = x * y, r = fma(-h0, g, 0.5);
+    const double h = fma(h0, r, h0), s = fma(g, r, g);
     return fma(fma(-s, s, x), h, s);
 }
 
