@@ -81,10 +81,6 @@ __device__ __forceinline__ void butterfly(float2 (&x)[R]) {
     }
 }
 
-// a / b for 0 <= a < 8192, 1 <= b <= 512 and inv = 1.0f / b: a + 1/2 is at least 1 / (2 b) away
-// from the next multiple of b, far more than the product's rounding.
-__device__ __forceinline__ int small_div(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
-
 template <int DIR, int R, bool FFAST, int E>
 __device__ __forceinline__ void stockham_stage(float2* buf, const float2* tw, int n, int count, int fstride,
                                                int estride, int p, int tid) {

@@ -7,10 +7,6 @@
 
 namespace vp {
 
-// a / b for integers with (float)(a + 1) exact and a quotient below 2^13, inv = 1.0f / b: a + 1/2
-// is at least 1 / (2 b) away from the next multiple of b, more than the product's rounding.
-__device__ __forceinline__ int small_div(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
-
 // ------------------------------------------------------------------ voxel-wise kernels
 
 // Operator TV/L1 gradient: grad (+)= tv_w grad TV + l1_w grad L1 (weights from the descriptor).

@@ -33,6 +33,10 @@ __device__ __forceinline__ AS1 T* glb(T* p) {
     return (AS1 T*)p;
 }
 
+// a / b for integers 0 <= a < 2^22, b >= 1 and inv = 1.0f / b: (a + 1/2) / b, exact but for two
+// roundings of (a / b) 2^-24 each, is at least 1 / (2 b) from a whole number, which is more.
+__device__ __forceinline__ int small_div(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
+
 // Field of the work item's slice descriptor (descriptor array or the inline copy).
 #define DF(field) (a.descs ? cst(a.descs + slice)->field : a.one.field)
 

@@ -245,7 +245,7 @@ hipError_t dense_forward(const DenseStep& ds, hipStream_t s) {
     hipError_t e;
     a.tasks = L.proj; a.ntasks = L.n_proj;
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, s)) != hipSuccess) return e;
-    return launch_blur(a, L, COL_STEP, false, s);
+    return launch_blur(a, L, COL_STEP, s);
 }
 
 hipError_t dense_adjoint(const DenseStep& ds, hipStream_t s) {

@@ -70,9 +70,9 @@ struct StageLists {
 inline bool blades_whole(const KArgs& a, const StageLists& L) {
     return !a.descs && L.segs.empty() && L.fft_n <= kBladeN;
 }
-// One slice's row and column passes: COL_STEP (work to work; without `back` the inverse rows may be
-// left out), COL_FORWARD (work to a.out0) or COL_ADJOINT (a.in0 to work).
-hipError_t launch_blur(KArgs a, const StageLists& L, int mode, bool back, hipStream_t s);
+// One slice's row and column passes: COL_STEP (work to work, the inverse rows left to the caller
+// unless blades_whole), COL_FORWARD (work to a.out0) or COL_ADJOINT (a.in0 to work).
+hipError_t launch_blur(KArgs a, const StageLists& L, int mode, hipStream_t s);
 
 StageLists plan_lists(const vp_plan* p, const DeviceTables* t, const Layout* L, const DeviceLayout* dl);
 // Whether a step over `voxels` voxels (summed over its slices) streams its state.

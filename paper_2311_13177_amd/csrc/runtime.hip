@@ -330,7 +330,7 @@ vp_status check_options(const vp_plan* p, const vp_options* o) {
 
 // ------------------------------------------------------------------ launch sequences
 
-hipError_t launch_blur(KArgs a, const StageLists& L, int mode, bool back, hipStream_t s) {
+hipError_t launch_blur(KArgs a, const StageLists& L, int mode, hipStream_t s) {
     a.mode = mode;
     if (blades_whole(a, L)) return launch_blades(a, s);
     hipError_t e = hipSuccess;
@@ -341,7 +341,7 @@ hipError_t launch_blur(KArgs a, const StageLists& L, int mode, bool back, hipStr
     if (mode != COL_ADJOINT) rows(-1);
     a.tasks = L.cols; a.ntasks = L.n_cols;
     if (e == hipSuccess) e = launch_cols(a, L.fft_n, L.lds_cols, s);
-    if (mode == COL_ADJOINT || (mode == COL_STEP && back)) rows(1);
+    if (mode == COL_ADJOINT) rows(1);
     return e;
 }
 
@@ -493,7 +493,7 @@ extern "C" vp_status vp_forward(const vp_plan* p, const vp_c64* d_vol, const vp_
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, sc.s)) != hipSuccess)
         return hip_status(e, "vp_forward project");
     a.out0 = (float2*)d_out;
-    return hip_status(launch_blur(a, L, COL_FORWARD, false, sc.s), "vp_forward DFT");
+    return hip_status(launch_blur(a, L, COL_FORWARD, sc.s), "vp_forward DFT");
 }
 
 extern "C" vp_status vp_adjoint(const vp_plan* p, const vp_c64* d_kres, vp_c64* d_grad, int32_t accumulate,
@@ -511,7 +511,7 @@ extern "C" vp_status vp_adjoint(const vp_plan* p, const vp_c64* d_kres, vp_c64* 
     const StageLists L = plan_lists(p, sc.t, sc.lay, sc.dl);
     hipError_t e;
     a.in0 = (const float2*)d_kres;
-    if ((e = launch_blur(a, L, COL_ADJOINT, true, sc.s)) != hipSuccess) return hip_status(e, "vp_adjoint DFT");
+    if ((e = launch_blur(a, L, COL_ADJOINT, sc.s)) != hipSuccess) return hip_status(e, "vp_adjoint DFT");
     a.tasks = L.gath; a.ntasks = L.n_gath;
     if ((e = launch_gather_lists(a, GATHER_STORE, L, sc.s)) != hipSuccess)
         return hip_status(e, "vp_adjoint gather");
@@ -604,7 +604,7 @@ extern "C" vp_status vp_forward_noalloc(const vp_plan* p, const vp_c64* d_vol, c
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, s)) != hipSuccess)
         return hip_status(e, "vp_forward_noalloc project");
     a.out0 = (float2*)d_out;
-    return hip_status(launch_blur(a, L, COL_FORWARD, false, s), "vp_forward_noalloc DFT");
+    return hip_status(launch_blur(a, L, COL_FORWARD, s), "vp_forward_noalloc DFT");
 }
 
 // Section 6 baselines: the coverage-weighted average (scaled by 1/n) into d_out, then the
@@ -1314,7 +1314,7 @@ vp_status session_objective_enqueue(vp_session* s, hipStream_t stream) {
     a.tasks = L.proj; a.ntasks = L.n_proj;
     if ((e = launch_project(a, L.tiles.proj_rows, L.tiles.proj_gw, L.tiles.proj_w, L.re_proj, L.odd, stream)) != hipSuccess)
         return hip_status(e, "objective");
-    if ((e = launch_blur(a, L, COL_STEP, false, stream)) != hipSuccess) return hip_status(e, "objective");
+    if ((e = launch_blur(a, L, COL_STEP, stream)) != hipSuccess) return hip_status(e, "objective");
     a.tasks = L.vox; a.ntasks = L.n_vox; a.dpart = s->dpart;
     if ((e = launch_reg_value(a, stream)) != hipSuccess) return hip_status(e, "objective");
     const size_t nl = loss_slots(p), nd = 2 * p->t_vox.size();
