@@ -208,7 +208,8 @@ vp_status vp_plan_knot(const vp_plan* plan, int32_t b, int32_t* knot, float* alp
 
 /* Exact device bytes one reconstruction of this plan allocates with these
  * options (volume ping-pong, Adam moments, blade work images, measurements,
- * tables, partial sums). Used for admission by memory budget. */
+ * tables, partial sums). Used for admission by memory budget. The workspaces that operator
+ * calls leave with a plan (at most four of at most 64 MiB) are not part of it. */
 vp_status vp_plan_device_bytes(const vp_plan* plan, const vp_options* opts, uint64_t* bytes);
 
 /* Autotuner: times every compiled tile shape that fits the plan on opts->device
@@ -285,7 +286,7 @@ vp_status vp_nu_adjoint(const vp_plan* plan, const vp_c64* d_samples, vp_c64* d_
 vp_status vp_nu_session_create(const vp_plan* plan, const vp_options* opts, const vp_c64* samples,
                                const vp_c64* init, vp_nu_session** out);
 
-/* n_steps optimiser steps (use_graph != 0: one captured step replayed), then waits. */
+/* n_steps optimiser steps (use_graph != 0: captured steps replayed), then waits. */
 vp_status vp_nu_session_step(vp_nu_session* session, int32_t n_steps, int32_t use_graph);
 
 /* Profiling: n_steps more steps eagerly with a HIP event around every stage; mean
@@ -371,8 +372,8 @@ vp_status vp_psnr(const vp_c64* d_image, const vp_c64* d_truth, int64_t n_px, in
 vp_status vp_session_create(const vp_plan* plan, const vp_options* opts, const vp_c64* kspace, const vp_c64* init,
                             vp_session** out);
 
-/* Runs n_steps optimiser steps on the device (use_graph != 0: one captured
- * step replayed) and waits for them. */
+/* Runs n_steps optimiser steps on the device (use_graph != 0: captured
+ * steps replayed) and waits for them. */
 vp_status vp_session_step(vp_session* session, int32_t n_steps, int32_t use_graph);
 
 /* Steps taken so far. */
@@ -428,7 +429,7 @@ typedef struct {
  * on opts[0]->device: each step is one launch per stage over the concatenated work
  * items of all slices (a block per work item, each reading its slice's descriptor
  * from a device table; the hardware dispatcher balances the uneven items), the whole
- * step captured once in a HIP graph and replayed. Every slice's result is
+ * steps captured in HIP graphs and replayed. Every slice's result is
  * the one vp_reconstruct gives it alone (bit for bit: summation orders do not
  * depend on the batch). Per-slice status goes to results[i]->status; the call
  * returns the first failure, if any. */
@@ -441,7 +442,7 @@ vp_status vp_batch_reconstruct(int32_t n, const vp_plan* const* plans, const vp_
  * batch's tile shape as vp_batch_reconstruct does and builds the concatenated work
  * lists; a slice that cannot be set up is reported by vp_batch_read (the call returns
  * its status, the others still run). *out stays NULL if no slice could be set up.
- * vp_batch_step runs n_steps batched steps (use_graph != 0: one captured step replayed;
+ * vp_batch_step runs n_steps batched steps (use_graph != 0: captured steps replayed;
  * slice i stops at opts[i]->n_steps) and waits. vp_batch_stage_times runs n_steps more
  * eagerly with a HIP event around each stage (stage_ms[5] as in vp_session_stage_times,
  * each stage one launch over all slices). vp_batch_read copies slice i's outputs and its
@@ -511,7 +512,7 @@ vp_status vp_kplanes_gradient(const vp_plan* plan, const vp_kplanes* model, cons
 vp_status vp_kplanes_session_create(const vp_plan* plan, const vp_kplanes* model, const vp_options* opts,
                                     const vp_c64* kspace, const vp_c64* init, vp_kplanes_session** out);
 
-/* n_steps optimiser steps (use_graph != 0: one captured step replayed); waits. */
+/* n_steps optimiser steps (use_graph != 0: captured steps replayed); waits. */
 vp_status vp_kplanes_session_step(vp_kplanes_session* session, int32_t n_steps, int32_t use_graph);
 
 /* Copies the parameters (params_out[count], may be NULL) and renders the model at the

@@ -24,9 +24,10 @@ constexpr double kMaxShift = 16.0;
 constexpr int kThreads = 256;
 
 // Projection and gather tiles: 64 columns (one per lane of a wave) by a per-layout
-// number of rows. A projection work item covers one tile for a group of up to 4 * GW
-// blade parts of one knot (parts dealt round-robin to the block's four waves); a gather
-// work item covers one tile for 4 * SC spectral bins (SC consecutive bins per wave).
+// number of rows. A projection work item covers one tile for a group of up to NW * GW
+// blade parts of one knot (parts dealt round-robin to the block's NW waves); a gather
+// work item covers one tile for NW * SC spectral bins (SC consecutive bins per wave);
+// NW is 4 or 8.
 // Rows, GW and SC are template parameters of the kernels; these are the compiled
 // combinations (at most 16 accumulators per lane).
 constexpr int kTileW = 64;
@@ -52,12 +53,12 @@ __host__ __device__ constexpr bool upd_tiles_ok(int sc) { return sc == 0 || sc =
 constexpr int kResRegion = 2048;
 constexpr int kResMaxParts = 32;
 constexpr size_t kResLds = 65536;
-// Staged region elements per thread (register prefetch depth of the LDS staging).
+// A staged region has at most kStageMax * kThreads elements. In the projection two planes of that
+// size are its ring of 64 KiB of LDS; in the gather kStageMax is the register prefetch depth.
 constexpr int kStageMax = 16;
-// A staged region of re elements (re <= kStageMax * kThreads) is loaded several planes
-// (bins or blade images) per barrier phase so that many loads are in flight: three
-// planes of up to 5 elements per thread, two of up to 8, or one of up to 16. The LDS
-// holds two phases (double buffering).
+// The gather loads a region of re elements several planes (blade images) per barrier phase so
+// that many loads are in flight: three planes of up to 5 elements per thread, two of up to 8, or
+// one of up to 16. The LDS holds two phases (double buffering).
 __host__ __device__ constexpr int stage_planes(int re) {
     return re <= 5 * kThreads ? 3 : (re <= 8 * kThreads ? 2 : 1);
 }
@@ -67,7 +68,7 @@ __host__ __device__ constexpr int stage_depth(int re) {
 __host__ __device__ constexpr size_t stage_lds_bytes(int re) {
     return 2 * (size_t)stage_planes(re) * (size_t)re * 8;
 }
-// Voxel-wise kernels (TV, render, objective): elements per work item.
+// Voxel-wise kernels (render, objective): elements per work item.
 constexpr int kVoxItem = 4096;
 
 // Rows per row-FFT work item and columns per column-FFT work item, as functions of n
@@ -109,7 +110,7 @@ struct KnotEntry {       // a blade part that reads (projection) / feeds (adjoin
     int pad;
 };
 
-struct ProjGroup {       // up to 4 * GW parts of one knot projected together
+struct ProjGroup {       // up to NW * GW parts of one knot projected together
     int knot, e0, ne;
     int ox_min, ox_max, oy_min, oy_max;
     int pad;
