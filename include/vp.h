@@ -428,7 +428,7 @@ typedef struct {
 /* Many independent slices, possibly of different sizes, reconstructed together
  * on opts[0]->device: each step is one launch per stage over the concatenated work
  * items of all slices (a block per work item, each reading its slice's descriptor
- * from a device table; the hardware dispatcher balances the uneven items), the whole
+ * from a device table; the hardware dispatcher balances the uneven items), whole
  * steps captured in HIP graphs and replayed. Every slice's result is
  * the one vp_reconstruct gives it alone (bit for bit: summation orders do not
  * depend on the batch). Per-slice status goes to results[i]->status; the call

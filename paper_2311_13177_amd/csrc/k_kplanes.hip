@@ -417,6 +417,13 @@ __global__ __launch_bounds__(64 * PARTS) void k_kp_grad_x(const KPDesc d) {
 // brought in.
 constexpr int kGyCols = 8;
 
+// Orders the LDS accesses of a wave's lanes among themselves: the hardware runs a wave's in order,
+// the fence keeps the compiler to it.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // PAIR: n is even and G on a 16-byte boundary, so that a lane's two columns are one access (a branch
 // at run time was compiled into four loads for both cases: 277 us instead of 200).
 template <int F, int BS, int PARTS, bool PAIR>
@@ -461,13 +468,13 @@ __global__ __launch_bounds__(64 * PARTS) void k_kp_grad_y(const KPDesc d) {
                     }
                 }
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_order();
 #pragma unroll
             for (int j = 0; j < BS; ++j)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     tile[j * (kTile / 2) + (i * 16 + lane / 4) * 4 + ((lane % 4) ^ (lane / 16))] = t[j][i];
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_order();
             const int xe = min(x0 + kGyCols, xb);
 #pragma unroll 1
             for (int x = x0; x < xe; ++x) {
