@@ -212,12 +212,11 @@ vp_status vp_plan_knot(const vp_plan* plan, int32_t b, int32_t* knot, float* alp
  * calls leave with a plan (at most four of at most 64 MiB) are not part of it. */
 vp_status vp_plan_device_bytes(const vp_plan* plan, const vp_options* opts, uint64_t* bytes);
 
-/* Autotuner: times every compiled tile shape that fits the plan on opts->device
- * (projection launches per projection shape; the fused gather/update per gather
- * shape; the gather that stores the data gradient per gather shape and the
- * separate update pass per update shape; a few repetitions each, on a scratch
- * reconstruction state with zero measurements; the optimiser and regulariser
- * settings of opts select the update that is timed),
+/* Autotuner: times steps with every compiled tile shape that fits the plan on opts->device
+ * (each projection shape, then each gather shape with the update fused and with a separate
+ * update pass, then each update shape; a few steps each in three rounds, the later ones over
+ * the shapes near the fastest, on a scratch reconstruction state with zero measurements; the
+ * optimiser and regulariser settings of opts select the update that is timed),
  * records the fastest shape for plans of the same sizes, shear extents and
  * optimiser in a process-wide table and returns it. Sessions, reconstructions,
  * batches and operators created later pick it up (vp_options.tiles all zero).

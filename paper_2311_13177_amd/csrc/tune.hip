@@ -1,4 +1,4 @@
-// Tile-shape autotuner of libvp: times the compiled projection and gather tile shapes
+// Tile-shape autotuner of libvp: times steps with the compiled projection and gather tile shapes
 // that fit a plan on the device and records the fastest per plan sizes. The shape only
 // changes how the work is cut into work items (every shape gives the same bits), so the
 // choice is purely a matter of speed.
@@ -47,25 +47,13 @@ int pow2_at_least(int v) {
     return r;
 }
 
-// Mean duration (ms) of `reps` launches after one untimed launch.
-template <class F>
-vp_status time_launches(hipStream_t s, int reps, F launch, float* ms) {
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    hipError_t e = hipEventCreate(&e0);
-    if (e == hipSuccess) e = hipEventCreate(&e1);
-    if (e == hipSuccess) e = launch();
-    if (e == hipSuccess) e = hipEventRecord(e0, s);
-    for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch();
-    if (e == hipSuccess) e = hipEventRecord(e1, s);
-    if (e == hipSuccess) e = hipEventSynchronize(e1);
-    if (e == hipSuccess) e = hipEventElapsedTime(ms, e0, e1);
-    if (e0) (void)hipEventDestroy(e0);
-    if (e1) (void)hipEventDestroy(e1);
-    if (e == hipSuccess) *ms /= (float)reps;
-    return hip_status(e, "autotune timing");
-}
-
-constexpr int kReps = 5;
+// Every candidate is timed as whole steps, kRoundSteps at a time in kRounds rounds over all of them
+// (the later ones over those near the fastest), by its least time. (Timed by itself, back to back, a kernel reads what its last launch has left in
+// the Infinity Cache, which a step has streamed through, and shapes change places: 192^2 x 32 bins x 16
+// knots in twelve rows takes 44 us in a step with eight waves, 49 with four, and its gather 192 us as
+// 4 x 4 with eight, 197 as 2 x 8 with four; back to back either won. One pass alone times the first
+// candidates while the clocks still rise.)
+constexpr int kRounds = 3, kRoundSteps = 2;
 
 }  // namespace
 
@@ -116,10 +104,84 @@ vp_status tune_plan(const vp_plan* p, const vp_options* o, Tiles* out) {
     std::unique_ptr<vp_session> s(raw);
     DeviceTables* tabs = s->tabs;
 
-    Tiles best = p->base_tiles;
-    best.upd_sc = 0;
+    if ((st = session_ensure_grad(s.get())) != VP_OK) return st;
+    struct Events {
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        ~Events() {
+            if (e0) (void)hipEventDestroy(e0);
+            if (e1) (void)hipEventDestroy(e1);
+        }
+    } ev;
+    e = hipEventCreate(&ev.e0);
+    if (e == hipSuccess) e = hipEventCreate(&ev.e1);
+    if (e != hipSuccess) return hip_status(e, "autotune events");
+
+    // A candidate: a shape that fits the plan, its step, and the least time seen (ms).
+    struct Candidate {
+        Tiles t;
+        StageLists lists;
+        KArgs a{};
+        float ms = FLT_MAX;
+    };
+    std::vector<Candidate> cand;
+    auto offer = [&](const Tiles& t) -> vp_status {
+        const Layout* L = nullptr;
+        const DeviceLayout* dl = nullptr;
+        if (plan_layout(p, t, &L) != VP_OK) {
+            clear_error();
+            return VP_OK;
+        }
+        const vp_status ls = device_layout(p, tabs, L, &dl);
+        if (ls != VP_OK) return ls;
+        Candidate c;
+        c.t = t;
+        c.lists = plan_lists(p, tabs, L, dl);
+        c.lists.epi = s->lists.epi;
+        c.lists.stream = s->lists.stream;
+        c.a.one = s->desc;
+        c.a.one.groups = dl->groups;
+        try {
+            cand.push_back(std::move(c));
+        } catch (const std::bad_alloc&) {
+            return fail(VP_ERR_NOMEM, "autotune: out of host memory");
+        }
+        return VP_OK;
+    };
+    // (a step of a blade-by-blade schedule has one blade's work: as many steps as blades, then)
+    const int steps = o->schedule == VP_SCHED_ALL_BLADES ? kRoundSteps : std::min(p->B, 16);
+    auto time_all = [&]() -> hipError_t {
+        float least = FLT_MAX;
+        for (int round = 0; round < kRounds; ++round)
+            for (Candidate& c : cand) {
+                if (round > 0 && c.ms > 1.1f * least) continue;  // out of reach
+                float ms = 0.f;
+                hipError_t te = hipEventRecord(ev.e0, s->stream);
+                for (int i = 0; i < steps && te == hipSuccess; ++i) launch_step(c.a, c.lists, s->stream, &te);
+                if (te == hipSuccess) te = hipEventRecord(ev.e1, s->stream);
+                if (te == hipSuccess) te = hipEventSynchronize(ev.e1);
+                if (te == hipSuccess) te = hipEventElapsedTime(&ms, ev.e0, ev.e1);
+                if (te != hipSuccess) return te;
+                c.ms = std::min(c.ms, ms);
+                least = std::min(least, c.ms);
+            }
+        return hipSuccess;
+    };
+    // Times the candidates and leaves the fastest one's shape and time.
+    auto choose = [&](Tiles* t, float* ms) -> vp_status {
+        if ((e = time_all()) != hipSuccess) return hip_status(e, "autotune timing");
+        for (const Candidate& c : cand)
+            if (c.ms < *ms) {
+                *ms = c.ms;
+                *t = c.t;
+            }
+        cand.clear();
+        return VP_OK;
+    };
+
     // projection: every compiled (rows, parts per wave) with four and with eight waves per
     // item that keeps every wave busy (eight only where a knot has more than four parts)
+    Tiles best = p->base_tiles;
+    best.upd_sc = 0;
     float best_ms = FLT_MAX;
     for (int waves = 4; waves <= 8; waves += 4) {
         if (waves == 8 && p->max_knot_parts <= 4) break;
@@ -131,128 +193,49 @@ vp_status tune_plan(const vp_plan* p, const vp_options* o, Tiles* out) {
                 t.proj_rows = rows;
                 t.proj_gw = gw;
                 t.proj_w = waves;
-                const Layout* L = nullptr;
-                const DeviceLayout* dl = nullptr;
-                if (plan_layout(p, t, &L) != VP_OK) {
-                    clear_error();
-                    continue;
-                }
-                if ((st = device_layout(p, tabs, L, &dl)) != VP_OK) return st;
-                KArgs a{};
-                a.one = s->desc;
-                a.one.groups = dl->groups;
-                a.tasks = dl->t_proj;
-                a.ntasks = (int)L->t_proj.size();
-                float ms = 0.f;
-                st = time_launches(
-                    s->stream, kReps,
-                    [&] { return launch_project(a, rows, gw, waves, L->re_proj, p->n & 1, s->stream); }, &ms);
-                if (st != VP_OK) return st;
-                if (ms < best_ms) {
-                    best_ms = ms;
-                    best.proj_rows = rows;
-                    best.proj_gw = gw;
-                    best.proj_w = waves;
-                }
+                if ((st = offer(t)) != VP_OK) return st;
             }
         }
     }
+    if ((st = choose(&best, &best_ms)) != VP_OK) return st;
     // gather: every compiled (rows, bins per wave) with four and with eight waves per item
-    // that keeps every wave busy, with the update fused (mode GATHER_STEP) and storing the
-    // data gradient for a separate update pass (GATHER_STORE); then every update-pass shape
-    if ((st = session_ensure_grad(s.get())) != VP_OK) return st;
-    float fused_ms = FLT_MAX, store_ms = FLT_MAX, upd_ms = FLT_MAX;
-    Tiles fused = best, split = best;
-    // (the fused update also with every part of a knot resident, where the layout allows it)
-    for (int mode = GATHER_STORE; mode <= GATHER_STEP; ++mode) {
-        for (int res = 0; res <= (mode == GATHER_STEP ? 1 : 0); ++res) {
-            for (int waves = 4; waves <= 8; waves += 4) {
-                // bins per wave up to the first power of two that covers S with every wave
-                const int sc_cap = std::min(8, pow2_at_least((p->S + waves - 1) / waves));
-                for (int rows = 2; rows <= 4; rows *= 2) {
-                    for (int sc = 1; sc <= sc_cap; sc *= 2) {
-                        if (!gath_tiles_ok(rows, sc, res == 1)) continue;
-                        Tiles t = p->base_tiles;
-                        t.gath_rows = rows;
-                        t.gath_sc = sc;
-                        t.gath_w = waves;
-                        t.upd_sc = 0;
-                        t.gath_res = res;
-                        const Layout* L = nullptr;
-                        const DeviceLayout* dl = nullptr;
-                        if (plan_layout(p, t, &L) != VP_OK) {
-                            clear_error();
-                            continue;
-                        }
-                        if ((st = device_layout(p, tabs, L, &dl)) != VP_OK) return st;
-                        KArgs a{};
-                        a.one = s->desc;
-                        a.epi = s->lists.epi;
-                        a.stream = s->lists.stream;
-                        a.tasks = dl->t_gath;
-                        a.ntasks = (int)L->t_gath.size();
-                        float ms = 0.f;
-                        st = time_launches(
-                            s->stream, kReps,
-                            [&] {
-                                return res ? launch_gather_res(a, mode, rows, sc, waves, L->re_gath, L->lds_res, s->stream)
-                                           : launch_gather(a, mode, rows, sc, waves, L->re_gath, s->stream);
-                            },
-                            &ms);
-                        if (st != VP_OK) return st;
-                        float& bm = mode == GATHER_STEP ? fused_ms : store_ms;
-                        Tiles& bt = mode == GATHER_STEP ? fused : split;
-                        if (ms < bm) {
-                            bm = ms;
-                            bt.gath_rows = rows;
-                            bt.gath_sc = sc;
-                            bt.gath_w = waves;
-                            bt.gath_res = res;
-                        }
-                    }
+    // that keeps every wave busy, with the update fused (also with every part of a knot resident, where
+    // the layout allows it), and storing the data gradient for a separate update pass; then every
+    // update-pass shape
+    auto offer_gathers = [&](bool resident, int upd_sc) -> vp_status {
+        for (int waves = 4; waves <= 8; waves += 4) {
+            // bins per wave up to the first power of two that covers S with every wave
+            const int sc_cap = std::min(8, pow2_at_least((p->S + waves - 1) / waves));
+            for (int rows = 2; rows <= 4; rows *= 2) {
+                for (int sc = 1; sc <= sc_cap; sc *= 2) {
+                    if (!gath_tiles_ok(rows, sc, resident)) continue;
+                    Tiles t = best;
+                    t.gath_rows = rows;
+                    t.gath_sc = sc;
+                    t.gath_w = waves;
+                    t.upd_sc = upd_sc;
+                    t.gath_res = resident;
+                    const vp_status os = offer(t);
+                    if (os != VP_OK) return os;
                 }
             }
         }
-    }
-    for (int usc = 2; usc <= 8; usc *= 2) {
-        Tiles t = p->base_tiles;
+        return VP_OK;
+    };
+    Tiles fused = best, split = best;
+    float fused_ms = FLT_MAX, split_ms = FLT_MAX;
+    for (bool resident : {false, true})
+        if ((st = offer_gathers(resident, 0)) != VP_OK) return st;
+    if ((st = choose(&fused, &fused_ms)) != VP_OK) return st;
+    if ((st = offer_gathers(false, 4)) != VP_OK) return st;
+    if ((st = choose(&split, &split_ms)) != VP_OK) return st;
+    for (int usc : {2, 8}) {
+        Tiles t = split;
         t.upd_sc = usc;
-        t.gath_res = 0;
-        t.gath_sc = std::min(t.gath_sc, 16 / t.gath_rows);
-        const Layout* L = nullptr;
-        const DeviceLayout* dl = nullptr;
-        if (plan_layout(p, t, &L) != VP_OK) {
-            clear_error();
-            continue;
-        }
-        if ((st = device_layout(p, tabs, L, &dl)) != VP_OK) return st;
-        KArgs a{};
-        a.one = s->desc;
-        a.epi = s->lists.epi;
-        a.stream = s->lists.stream;
-        a.tasks = dl->t_upd;
-        a.ntasks = (int)L->t_upd.size();
-        float ms = 0.f;
-        st = time_launches(s->stream, kReps, [&] { return launch_update(a, usc, s->stream); }, &ms);
-        if (st != VP_OK) return st;
-        if (ms < upd_ms) {
-            upd_ms = ms;
-            split.upd_sc = usc;
-        }
+        if ((st = offer(t)) != VP_OK) return st;
     }
-    if (store_ms + upd_ms < fused_ms) {
-        best.gath_rows = split.gath_rows;
-        best.gath_sc = split.gath_sc;
-        best.gath_w = split.gath_w;
-        best.upd_sc = split.upd_sc;
-        best.gath_res = 0;
-    } else {
-        best.gath_rows = fused.gath_rows;
-        best.gath_sc = fused.gath_sc;
-        best.gath_w = fused.gath_w;
-        best.upd_sc = 0;
-        best.gath_res = fused.gath_res;
-    }
+    if ((st = choose(&split, &split_ms)) != VP_OK) return st;
+    best = split_ms < fused_ms ? split : fused;
     if ((e = hipStreamSynchronize(s->stream)) != hipSuccess) return hip_status(e, "autotune");
     {
         std::lock_guard<std::mutex> lk(g_mu);
